@@ -59,11 +59,11 @@ struct dfacto_group {
     bool reuse_grams = false;   // BF16 storage
     bool own_factors = false;   // DFACTO_GROUP_OWN_FACTORS
     bool grams_valid = false;   // an iteration has run since creation
-    // One grouped MTTKRP launch per kernel class and mode: its shape (columns
-    // per lane, lanes per group), chunks per lane group, work items (one
-    // table per item size) and persistent grid size.  The fix-ups after it
-    // keep the class's own shape (the carries do not depend on the one the
-    // MTTKRP ran with).  cands: the launch forms the tuner may choose.
+    // One grouped MTTKRP launch per kernel class and mode: its lane groups
+    // (columns per lane, lanes per group), chunks per lane group, work items
+    // (one table per item size) and persistent grid size.  The fix-ups after
+    // it run in the class's shape (the carries do not depend on the lane
+    // groups the MTTKRP ran with).  cands: the forms the tuner may choose.
     struct MtVariant {
         MttkrpShape sh;
         unsigned kper;
@@ -72,7 +72,6 @@ struct dfacto_group {
     };
     struct MtLaunch {
         MtVariant v;
-        bool small;
         unsigned grid;
         std::vector<MtVariant> cands;
     };
@@ -297,26 +296,28 @@ struct Build {
                 });
                 g->launches += 2;
             }
-            // launch forms per class: the default shape and, when tuning,
-            // other columns per lane (fewer, or eight for BF16), lanes per
-            // group to match, and 2 or 4 chunks per lane group; one
-            // work-item table per item size
+            // launch forms per class: the default lane groups and, when
+            // tuning, other columns per lane (up to the class's, or eight
+            // for BF16), lanes per group to match, and 2 or 4 chunks per
+            // lane group; one work-item table per item size
             const bool tune = tuning;
-            auto forms = [tune, dt](const MttkrpShape &sh, const std::vector<int> &ranks) {
+            auto forms = [tune, dt, grp](const MttkrpShape &cl, const std::vector<int> &ranks,
+                                         int64_t nchunk) {
+                const int widest = *std::max_element(ranks.begin(), ranks.end());
+                const MttkrpShape sh = mttkrp_main_shape(&grp->gctx, cl, widest, dt, nchunk);
                 std::vector<std::pair<MttkrpShape, unsigned>> f{{sh, 1u}};
                 if (!tune) return f;
                 std::vector<MttkrpShape> shapes{sh};
                 // BF16 rows of a multiple of 8 columns: also 8 columns per
                 // lane (one 16-byte load; the factors are 16-byte aligned)
-                bool wide = dt == DFACTO_BF16 && sh.nch == 1 && sh.cpl < 8;
+                bool wide = dt == DFACTO_BF16 && sh.nch == 1;
                 for (int r : ranks) wide = wide && r % 8 == 0;
-                const int top = wide ? 8 : sh.cpl / 2;
+                const int top = wide ? 8 : cl.cpl;
                 for (int c = top; sh.nch == 1 && c >= 1; c /= 2) {
                     if (c == sh.cpl) continue;
                     // lanes per group: enough for the widest member (the
                     // lanes past a member's columns stay idle)
-                    int lanes = 1;
-                    for (int r : ranks) lanes = std::max(lanes, (r + c - 1) / c);
+                    const int lanes = (widest + c - 1) / c;
                     int gv = 2;
                     while (gv < lanes) gv <<= 1;
                     if (gv <= 64) shapes.push_back({c, gv, 1});
@@ -328,13 +329,13 @@ struct Build {
             };
             struct Cls {
                 MttkrpShape sh;
-                bool small;
                 std::vector<int> ranks;
+                int64_t nchunk = 0;
                 std::map<unsigned, Expansion<uint2>> items;  // by chunks per item
                 Expansion<uint2> empty;
                 Expansion<uint4> shortr, longr;
             };
-            std::map<std::tuple<int, int, int, bool>, Cls> cls;
+            std::map<std::tuple<int, int, int>, Cls> cls;
             for (int t = 0; t < n; ++t) {
                 const ModeData &md = T[t]->mode[m];
                 const void *Fl = F[3 * t + md.leaf], *Fm = F[3 * t + md.mid];
@@ -344,11 +345,10 @@ struct Build {
                            ws[t].M, ws[t].carry};
                 const MttkrpShape sh =
                     mttkrp_shape(R[t], dt, Fl, Fm, ws[t].M, ws[t].perm && md.perm_leaf);
-                const bool sm = mttkrp_small(T[t], m);
-                Cls &c = cls[{sh.cpl, sh.g, sh.nch, sm}];
+                Cls &c = cls[{sh.cpl, sh.g, sh.nch}];
                 c.sh = sh;
-                c.small = sm;
                 c.ranks.push_back(R[t]);
+                c.nchunk += md.nchunk;
                 c.shortr.add(t, md.runs_short, md.nruns_short, 3, 0);
                 c.longr.add(t, md.runs_long, md.nruns_long, 3, 0);
                 c.empty.add(t, md.empty_rows, md.nempty, 1, 0);
@@ -358,7 +358,7 @@ struct Build {
             // empty rows from the members' own device lists
             for (auto &kv : cls) {
                 Cls &c = kv.second;
-                for (const auto &f : forms(c.sh, c.ranks)) {
+                for (const auto &f : forms(c.sh, c.ranks, c.nchunk)) {
                     const unsigned per = mttkrp_group_chunks_per_item(f.first, f.second);
                     if (c.items.count(per)) continue;
                     Expansion<uint2> &x = c.items[per];
@@ -367,9 +367,7 @@ struct Build {
                         const MttkrpShape sh =
                             mttkrp_shape(R[t], dt, desc[t].Fleaf, desc[t].Fmid, ws[t].M,
                                          ws[t].perm && md.perm_leaf);
-                        if (sh.cpl != c.sh.cpl || sh.g != c.sh.g || sh.nch != c.sh.nch ||
-                            mttkrp_small(T[t], m) != c.small)
-                            continue;
+                        if (sh.cpl != c.sh.cpl || sh.g != c.sh.g || sh.nch != c.sh.nch) continue;
                         x.add(t, nullptr, (md.nchunk + per - 1) / per, 0, per);
                     }
                 }
@@ -378,10 +376,8 @@ struct Build {
             for (auto &kv : cls) {
                 Cls &c = kv.second;
                 const MttkrpShape sh = c.sh;
-                const bool sm = c.small;
                 dfacto_group::MtLaunch L;
-                L.small = sm;
-                for (const auto &f : forms(c.sh, c.ranks)) {
+                for (const auto &f : forms(c.sh, c.ranks, c.nchunk)) {
                     const Expansion<uint2> &x = c.items[mttkrp_group_chunks_per_item(f.first, f.second)];
                     L.cands.push_back({f.first, f.second, nullptr, (uint32_t)x.total});
                 }
@@ -394,7 +390,7 @@ struct Build {
                 const size_t gi = g->mt.size() - 1;
                 auto step = [grp, dt, dd, gi] {
                     const dfacto_group::MtLaunch &l = grp->mt[gi];
-                    launch_mttkrp_group(&grp->gctx, dt, l.v.sh, l.small, dd, l.v.items,
+                    launch_mttkrp_group(&grp->gctx, dt, l.v.sh, dd, l.v.items,
                                         l.v.nitems, l.grid, l.v.kper);
                 };
                 g->steps.push_back(step);

@@ -383,10 +383,13 @@ int kernel_cols(const dfacto_tensor *t, int R, dfacto_dtype dtype);
 // relabeled: the mode gathers through rank-ordered copies
 MttkrpShape mttkrp_shape(int R, dfacto_dtype dtype, const void *Fleaf, const void *Fmid,
                          const float *out, bool relabeled);
+// the lane groups the main kernel runs in for that (fix-up) shape, over nchunk chunks
+MttkrpShape mttkrp_main_shape(const dfacto_ctx *ctx, const MttkrpShape &sh, int R,
+                              dfacto_dtype dtype, int64_t nchunk);
 bool mttkrp_small(const dfacto_tensor *t, int mode);
 // chunks per work item of the grouped MTTKRP: kper per lane group
 unsigned mttkrp_group_chunks_per_item(const MttkrpShape &sh, unsigned kper);
-void launch_mttkrp_group(dfacto_ctx *ctx, dfacto_dtype dtype, const MttkrpShape &sh, bool small,
+void launch_mttkrp_group(dfacto_ctx *ctx, dfacto_dtype dtype, const MttkrpShape &sh,
                          const GroupMttkrp *d_desc, const uint2 *d_items, uint32_t nitems,
                          unsigned grid, unsigned kper);
 void launch_fix_group(dfacto_ctx *ctx, const MttkrpShape &sh, const GroupMttkrp *d_desc,

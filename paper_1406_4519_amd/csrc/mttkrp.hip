@@ -39,9 +39,6 @@ namespace {
 #ifndef DFACTO_NT_STREAM
 #define DFACTO_NT_STREAM 0
 #endif
-#ifndef DFACTO_SHARE_ENTRIES
-#define DFACTO_SHARE_ENTRIES 1
-#endif
 // At least 5 waves per SIMD: the gathers are latency-bound, and the FP32
 // CPL = 4 kernel sits right at the 96-register limit for 5 waves.  Whole-wave
 // groups (G = 64) keep the compiler's choice (they would spill).
@@ -327,22 +324,21 @@ struct BufLoad<uint16_t, 1> {
     }
 };
 
-// ---- main kernel ---------------------------------------------------------
-// One work chunk (gid) per lane group of G lanes (lane = 0 .. G-1), its
-// factor rows from `src`.
-// RES: the residual form used by the joint model's ratings term: each
-// nonzero's value x becomes x - xhat with xhat = sum_r F_root[root, r]
-// F_mid[mid, r] F_leaf[leaf, r] (the CP model at that entry), so the output
-// is the MTTKRP of the residual restricted to the stored entries.  The dot
+// ---- residual kernel -------------------------------------------------------
+// The joint model's ratings term: the MTTKRP with each nonzero's value x
+// replaced by x - xhat, xhat = sum_r F_root[root, r] F_mid[mid, r]
+// F_leaf[leaf, r] (the CP model at that entry), so the output is the MTTKRP
+// of the residual restricted to the stored entries.  One work chunk (gid) per
+// lane group of G lanes (lane = 0 .. G-1), its factor rows from `src`; the dot
 // product is reduced across the group's lanes by xor shuffles (every lane
 // ends with the same sum: each step adds two commuted operands).
-template <typename T, int CPL, int G, int NCH, bool SMALL, bool RES = false, class Src>
-__device__ __forceinline__ void mttkrp_chunk(const uint2 *__restrict__ st_,
-                                             const uint32_t *__restrict__ cstart, uint32_t nchunk,
-                                             const Src &src, int R,
-                                             float *__restrict__ out_, float *__restrict__ carry_,
-                                             uint32_t gid, int lane,
-                                             const T *__restrict__ Froot = nullptr) {
+template <typename T, int CPL, int G, int NCH, bool SMALL, class Src>
+__device__ __forceinline__ void mttkrp_res_chunk(const uint2 *__restrict__ st_,
+                                                 const uint32_t *__restrict__ cstart,
+                                                 uint32_t nchunk, const Src &src, int R,
+                                                 float *__restrict__ out_,
+                                                 float *__restrict__ carry_, uint32_t gid,
+                                                 int lane, const T *__restrict__ Froot) {
     if (gid >= nchunk) return;
     const uint32_t cs = gptr(cstart)[gid], ce = gptr(cstart)[gid + 1];
     if (cs >= ce) return;
@@ -357,14 +353,14 @@ __device__ __forceinline__ void mttkrp_chunk(const uint2 *__restrict__ st_,
     for (int c = 0; c < NCH; ++c) {
         col[c] = (c * G + lane) * CPL;
         act[c] = col[c] < R;
-        rootb[c] = RES ? gptr(Froot) + (act[c] ? col[c] : 0) : nullptr;
+        rootb[c] = gptr(Froot) + (act[c] ? col[c] : 0);
     }
     auto row_off = [&](uint32_t idx) -> size_t {
         if constexpr (SMALL) return (size_t)(uint32_t)__umul24(idx, (uint32_t)R);
         else return (size_t)idx * (size_t)R;
     };
     float acc[NCH][CPL], p[NCH][CPL], mrow[NCH][CPL];
-    float rrow[RES ? NCH : 1][CPL];  // the root's factor row (RES only)
+    float rrow[NCH][CPL];  // the root's factor row
     const uint2 h0 = load_entry(st + cs);
     uint32_t row = h0.y;
     bool cont = !(h0.x & kRootBit);
@@ -373,7 +369,7 @@ __device__ __forceinline__ void mttkrp_chunk(const uint2 *__restrict__ st_,
 #pragma unroll
         for (int q = 0; q < CPL; ++q) acc[c][q] = p[c][q] = 0.f;
         src.load(h0, c, mrow[c]);  // h0 is a header: its mid row
-        if constexpr (RES) RowLoad<T, CPL>::load(rootb[c] + row_off(row), rrow[c]);
+        RowLoad<T, CPL>::load(rootb[c] + row_off(row), rrow[c]);
     }
 
     auto flush = [&](uint32_t r_out, bool is_cont) {
@@ -403,18 +399,15 @@ __device__ __forceinline__ void mttkrp_chunk(const uint2 *__restrict__ st_,
     // F_leaf[leaf].
     auto step = [&](const uint2 &w, const float (&g)[NCH][CPL]) {
         const bool hdr = (int32_t)w.x < 0;
-        float v = hdr ? 0.f : __uint_as_float(w.y);
-        if constexpr (RES) {
-            float part = 0.f;
+        float part = 0.f;
 #pragma unroll
-            for (int c = 0; c < NCH; ++c)
+        for (int c = 0; c < NCH; ++c)
 #pragma unroll
-                for (int q = 0; q < CPL; ++q)
-                    part = fmaf(act[c] ? rrow[c][q] * mrow[c][q] : 0.f, g[c][q], part);
+            for (int q = 0; q < CPL; ++q)
+                part = fmaf(act[c] ? rrow[c][q] * mrow[c][q] : 0.f, g[c][q], part);
 #pragma unroll
-            for (int o = G / 2; o > 0; o >>= 1) part += __shfl_xor(part, o, G);
-            v = hdr ? 0.f : v - part;
-        }
+        for (int o = G / 2; o > 0; o >>= 1) part += __shfl_xor(part, o, G);
+        const float v = hdr ? 0.f : __uint_as_float(w.y) - part;
 #pragma unroll
         for (int c = 0; c < NCH; ++c)
 #pragma unroll
@@ -432,10 +425,8 @@ __device__ __forceinline__ void mttkrp_chunk(const uint2 *__restrict__ st_,
                 for (int q = 0; q < CPL; ++q) acc[c][q] = 0.f;
             cont = false;
             row = w.y;
-            if constexpr (RES) {
 #pragma unroll
-                for (int c = 0; c < NCH; ++c) RowLoad<T, CPL>::load(rootb[c] + row_off(row), rrow[c]);
-            }
+            for (int c = 0; c < NCH; ++c) RowLoad<T, CPL>::load(rootb[c] + row_off(row), rrow[c]);
         }
     };
 
@@ -444,7 +435,7 @@ __device__ __forceinline__ void mttkrp_chunk(const uint2 *__restrict__ st_,
     // group shares them through ds_swizzle (the LDS crossbar), so the vector
     // memory path carries each entry once instead of once per lane.  A
     // 64-lane group is the whole wave and loads the batch directly.
-    constexpr bool kShare = G <= 32 && DFACTO_SHARE_ENTRIES;
+    constexpr bool kShare = G <= 32;
     constexpr int KL = kShare ? (kUnroll + G - 1) / G : kUnroll;  // entries held per lane
     auto load_batch = [&](uint32_t at, uint2 (&wl)[KL]) {
 #pragma unroll
@@ -497,15 +488,304 @@ __device__ __forceinline__ void mttkrp_chunk(const uint2 *__restrict__ st_,
     flush(row, cont);
 }
 
-template <typename T, int CPL, int G, int NCH, bool SMALL>
+// ---- main kernel: lane groups with execution masks -------------------------
+// One work chunk per group of G lanes, CPL columns per lane (NCH blocks of
+// them for a whole wave, G = 64).  A wave's groups meet headers and nonzeros at
+// different entries, so selecting per lane what each entry does cost 22 of the
+// 45 vector instructions per entry.  Here what an entry does is kept as
+// execution masks: one ballot per batch tells which lanes' entries are
+// headers, and for each entry the scalar unit spreads its bit over every
+// group's lanes; a masked FMA then costs one vector instruction per column
+// and nothing where it does not apply (about 20 per entry in all).  The lane
+// that loads an entry also forms its row's address, once for its group.
+// What bounds it at scale: lines past L2, 128 bytes for every gathered row
+// that misses (R = 8 to 32 take the same time), at about 6 TB/s.  Three modes
+// of the 50M-nonzero Zipf(1.1) tensor: R = 32 FP32 2140 -> 2060 us, BF16
+// 2046 -> 1905, R = 8 2181 -> 1799; 100M nonzeros relabeled, R = 32 BF16
+// 3244 -> 2948, R = 10 FP32 3108 -> 3043, R = 100 BF16 11018 -> 8250.
+//
+// p += v * g in the lanes of `m` (V: the constraint of v, "v" or "s")
+#define DF_MASKED_ADD(V)                                                                       \
+    if constexpr (CPL == 1) {                                                                  \
+        asm("s_mov_b64 exec, %[m]\n\t"                                                         \
+            "v_fmac_f32 %[p0], %[v], %[g0]\n\t"                                                \
+            "s_mov_b64 exec, -1"                                                               \
+            : [p0] "+v"(p[0])                                                                  \
+            : [m] "s"(m), [v] V(v), [g0] "v"(g[0]));                                           \
+    } else if constexpr (CPL == 2) {                                                           \
+        asm("s_mov_b64 exec, %[m]\n\t"                                                         \
+            "v_fmac_f32 %[p0], %[v], %[g0]\n\t"                                                \
+            "v_fmac_f32 %[p1], %[v], %[g1]\n\t"                                                \
+            "s_mov_b64 exec, -1"                                                               \
+            : [p0] "+v"(p[0]), [p1] "+v"(p[1])                                                 \
+            : [m] "s"(m), [v] V(v), [g0] "v"(g[0]), [g1] "v"(g[1]));                           \
+    } else {                                                                                   \
+        for (int q = 0; q < CPL; q += 4)                                                       \
+            asm("s_mov_b64 exec, %[m]\n\t"                                                     \
+                "v_fmac_f32 %[p0], %[v], %[g0]\n\t"                                            \
+                "v_fmac_f32 %[p1], %[v], %[g1]\n\t"                                            \
+                "v_fmac_f32 %[p2], %[v], %[g2]\n\t"                                            \
+                "v_fmac_f32 %[p3], %[v], %[g3]\n\t"                                            \
+                "s_mov_b64 exec, -1"                                                           \
+                : [p0] "+v"(p[q]), [p1] "+v"(p[q + 1]), [p2] "+v"(p[q + 2]),                   \
+                  [p3] "+v"(p[q + 3])                                                          \
+                : [m] "s"(m), [v] V(v), [g0] "v"(g[q]), [g1] "v"(g[q + 1]),                    \
+                  [g2] "v"(g[q + 2]), [g3] "v"(g[q + 3]));                                     \
+    }
+template <int CPL>
+__device__ __forceinline__ void masked_add(uint64_t m, float v, const float (&g)[CPL],
+                                           float (&p)[CPL]) {
+    DF_MASKED_ADD("v")
+}
+template <int CPL>  // v uniform
+__device__ __forceinline__ void masked_add_s(uint64_t m, uint32_t v, const float (&g)[CPL],
+                                             float (&p)[CPL]) {
+    DF_MASKED_ADD("s")
+}
+#undef DF_MASKED_ADD
+
+// acc += p * mrow, p = 0 * g + 0, mrow = g in the lanes of `m`
+template <int CPL>
+__device__ __forceinline__ void masked_close(uint64_t m, const float (&g)[CPL], float (&p)[CPL],
+                                             float (&acc)[CPL], float (&mrow)[CPL]) {
+    if constexpr (CPL == 1) {
+        asm("s_mov_b64 exec, %[m]\n\t"
+            "v_fmac_f32 %[a0], %[p0], %[r0]\n\t"
+            "v_fma_f32 %[p0], 0, %[g0], 0\n\t"
+            "v_mov_b32 %[r0], %[g0]\n\t"
+            "s_mov_b64 exec, -1"
+            : [a0] "+v"(acc[0]), [p0] "+v"(p[0]), [r0] "+v"(mrow[0])
+            : [m] "s"(m), [g0] "v"(g[0]));
+    } else {
+        for (int q = 0; q < CPL; q += 2)
+            asm("s_mov_b64 exec, %[m]\n\t"
+                "v_fmac_f32 %[a0], %[p0], %[r0]\n\t"
+                "v_fmac_f32 %[a1], %[p1], %[r1]\n\t"
+                "v_fma_f32 %[p0], 0, %[g0], 0\n\t"
+                "v_fma_f32 %[p1], 0, %[g1], 0\n\t"
+                "v_mov_b32 %[r0], %[g0]\n\t"
+                "v_mov_b32 %[r1], %[g1]\n\t"
+                "s_mov_b64 exec, -1"
+                : [a0] "+v"(acc[q]), [a1] "+v"(acc[q + 1]), [p0] "+v"(p[q]), [p1] "+v"(p[q + 1]),
+                  [r0] "+v"(mrow[q]), [r1] "+v"(mrow[q + 1])
+                : [m] "s"(m), [g0] "v"(g[q]), [g1] "v"(g[q + 1]));
+    }
+}
+
+// the bits of `b` (one per G-lane group, at the group's first lane) spread
+// over the lanes of their groups
+template <int G>
+__device__ __forceinline__ uint64_t spread_groups(uint64_t b) {
+    if constexpr (G == 64) {
+        return (b & 1) ? ~0ull : 0ull;
+    } else {
+        constexpr uint32_t k = G == 32 ? 0xFFFFFFFFu : (1u << (G & 31)) - 1u;
+        return ((uint64_t)((uint32_t)(b >> 32) * k) << 32) | (uint32_t)((uint32_t)b * k);
+    }
+}
+
+// Entries per batch: as many rows in flight as the registers allow.  FP32 rows
+// at four columns per lane keep two batches of eight (one batch is gathered
+// while the other is added up: R = 32, 50M nonzeros 2112 -> 2058 us; 16 in one
+// batch spill, 3170); narrower ones one batch of 16 (R = 16: 1885 us against
+// 1965 at 8, 2008 at 24, and 3028 with two batches).
+template <typename T, int CPL, int G, int NCH>
+constexpr int batch_entries() {
+    if (G == 64) return CPL * NCH == 1 ? 32 : (CPL * NCH == 2 ? 16 : 8);
+    return CPL <= 2 || (CPL == 4 && sizeof(T) == 2) ? 16 : 8;
+}
+
+template <typename T, int CPL, int G, int NCH>
+__device__ __forceinline__ void mttkrp_group_chunk(const uint2 *__restrict__ st_,
+                                                   const uint32_t *__restrict__ cstart,
+                                                   uint32_t nchunk, const T *__restrict__ Fleaf,
+                                                   const T *__restrict__ Fmid, int R,
+                                                   float *__restrict__ out_,
+                                                   float *__restrict__ carry_, uint32_t gid,
+                                                   int lane) {
+    constexpr bool WAVE = G == 64;
+    constexpr int U = batch_entries<T, CPL, G, NCH>();
+    constexpr int KL = (U + G - 1) / G;  // entries held per lane
+    constexpr uint64_t kFirst = G == 2    ? 0x5555555555555555ull
+                                : G == 4  ? 0x1111111111111111ull
+                                : G == 8  ? 0x0101010101010101ull
+                                : G == 16 ? 0x0001000100010001ull
+                                : G == 32 ? 0x0000000100000001ull
+                                          : 1ull;
+    const DF_GLOBAL uint2 *__restrict__ st = gptr(st_);
+    DF_GLOBAL float *__restrict__ out = gptr(out_);
+    DF_GLOBAL float *__restrict__ carry = gptr(carry_);
+    // every lane of the wave stays active: a group without a chunk walks an
+    // empty one
+    if constexpr (WAVE) gid = __builtin_amdgcn_readfirstlane(gid);
+    const uint32_t gc = gid < nchunk ? gid : nchunk - 1;
+    uint32_t cs = gptr(cstart)[gc], ce = gptr(cstart)[gc + 1];
+    if constexpr (WAVE) {
+        cs = __builtin_amdgcn_readfirstlane(cs);
+        ce = __builtin_amdgcn_readfirstlane(ce);
+    }
+    const bool live = gid < nchunk && cs < ce;
+    const uint32_t last = live ? ce : cs;  // == cs: nothing to do
+    // lanes past the last column repeat the group's first lane's
+    int col[NCH];
+    uint32_t colb[NCH];
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+        col[c] = (c * G + lane) * CPL;
+        if (col[c] >= R) col[c] = 0;
+        colb[c] = (uint32_t)col[c] * (uint32_t)sizeof(T);
+    }
+    const uint32_t rowb = (uint32_t)R * (uint32_t)sizeof(T);
+    uint32_t nmax = live ? ce - cs - 1 : 0u, nmin = nmax;
+    if constexpr (!WAVE) {
+#pragma unroll
+        for (int o = G; o < 64; o <<= 1) {
+            nmax = max(nmax, (uint32_t)__shfl_xor((int)nmax, o));
+            nmin = min(nmin, (uint32_t)__shfl_xor((int)nmin, o));
+        }
+        nmax = __builtin_amdgcn_readfirstlane(nmax);
+        nmin = __builtin_amdgcn_readfirstlane(nmin);
+    }
+
+    auto fetch = [&](uint32_t at, uint2 (&wl)[KL]) {
+#pragma unroll
+        for (int k = 0; k < KL; ++k) {
+            const uint32_t e = at + (uint32_t)lane + G * k;
+            wl[k] = load_entry(st + (e < last ? e : last));
+        }
+    };
+    float acc[NCH][CPL], p[NCH][CPL], mrow[NCH][CPL];
+    const uint2 h0 = load_entry(st + cs);
+    DF_GLOBAL float *dst[NCH];
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+#pragma unroll
+        for (int q = 0; q < CPL; ++q) acc[c][q] = p[c][q] = 0.f;
+        RowLoad<T, CPL>::load(
+            (const DF_GLOBAL T *)((const DF_GLOBAL char *)gptr(Fmid) + colb[c] +
+                                  (uint64_t)(live ? h0.x & kIdxMask : 0u) * rowb),
+            mrow[c]);
+        dst[c] = ((h0.x & kRootBit) ? out + (size_t)h0.y * R : carry + (size_t)gc * R) + col[c];
+    }
+
+    struct Batch {
+        uint64_t hdr[KL], nz[KL], root[KL];
+        uint32_t y[KL];
+        float g[U][NCH][CPL];
+    };
+    auto bcast = [&](uint32_t x, auto uc) -> uint32_t {
+        constexpr int u = decltype(uc)::value;
+        if constexpr (WAVE) {
+            return (uint32_t)__builtin_amdgcn_readlane((int)x, u);
+        } else {
+            // bit-mask swizzle: source lane = (lane & ~(G-1)) | (u % G), within 32 lanes
+            constexpr int pat = (0x1F & ~(G - 1)) | ((u % G) << 5);
+            return (uint32_t)__builtin_amdgcn_ds_swizzle((int)x, pat);
+        }
+    };
+    auto issue = [&](Batch &b, uint32_t at, const uint2 (&wl)[KL]) {
+        uint32_t lo[KL], hi[KL];
+#pragma unroll
+        for (int k = 0; k < KL; ++k) {
+            const bool v = at + (uint32_t)lane + G * k < last;
+            const bool h = (int32_t)wl[k].x < 0;
+            const uint64_t a = (uint64_t)(uintptr_t)(h ? Fmid : Fleaf) +
+                               (uint64_t)(wl[k].x & kIdxMask) * rowb;
+            lo[k] = (uint32_t)a;
+            hi[k] = (uint32_t)(a >> 32);
+            b.hdr[k] = __ballot(v && h);
+            b.nz[k] = __ballot(v && !h);
+            b.root[k] = __ballot(v && h && (wl[k].x & kRootBit));
+            b.y[k] = wl[k].y;
+        }
+        static_for<0, U>([&](auto uc) {
+            constexpr int u = decltype(uc)::value;
+            const uint32_t l = bcast(lo[u / G], uc), h = bcast(hi[u / G], uc);
+            const DF_GLOBAL char *a =
+                (const DF_GLOBAL char *)(uintptr_t)(((uint64_t)h << 32) | l);
+#pragma unroll
+            for (int c = 0; c < NCH; ++c)
+                RowLoad<T, CPL>::load((const DF_GLOBAL T *)(a + colb[c]), b.g[u][c]);
+        });
+    };
+    auto add = [&](const Batch &b, auto fullc) {
+        static_for<0, U>([&](auto uc) {
+            constexpr int u = decltype(uc)::value;
+            constexpr int k = u / G, sh = u % G;
+            constexpr bool full = decltype(fullc)::value;
+            const uint32_t y = bcast(b.y[k], uc);
+            const uint64_t hm = spread_groups<G>((b.hdr[k] >> sh) & kFirst);
+            const uint64_t nm = full ? ~hm : spread_groups<G>((b.nz[k] >> sh) & kFirst);
+#pragma unroll
+            for (int c = 0; c < NCH; ++c) {
+                if constexpr (WAVE) masked_add_s<CPL>(nm, y, b.g[u][c], p[c]);
+                else masked_add<CPL>(nm, __uint_as_float(y), b.g[u][c], p[c]);
+                masked_close<CPL>(hm, b.g[u][c], p[c], acc[c], mrow[c]);
+            }
+            const uint64_t rb = (b.root[k] >> sh) & kFirst;
+            if (rb) {
+                if (WAVE || __builtin_amdgcn_inverse_ballot_w64(spread_groups<G>(rb))) {
+#pragma unroll
+                    for (int c = 0; c < NCH; ++c) {
+                        store_vec<CPL>(dst[c], acc[c]);
+#pragma unroll
+                        for (int q = 0; q < CPL; ++q) acc[c][q] = 0.f;
+                        dst[c] = out + (size_t)y * R + col[c];
+                    }
+                }
+            }
+        });
+    };
+    uint2 wn[KL];
+    fetch(cs + 1, wn);
+    if constexpr (WAVE || (CPL == 4 && sizeof(T) == 4)) {
+        // Each batch's entries are requested before the rows of the batch
+        // ahead of it, so that waiting for them leaves those rows in flight.
+        if (nmax > 0) {
+            uint2 wm[KL];
+            Batch a, b;
+            fetch(cs + 1 + U, wm);
+            issue(a, cs + 1, wn);
+            for (uint32_t i = 0; i < nmax; i += 2 * U) {
+                fetch(cs + 1 + i + 2 * U, wn);
+                issue(b, cs + 1 + i + U, wm);
+                add(a, std::false_type{});
+                fetch(cs + 1 + i + 3 * U, wm);
+                issue(a, cs + 1 + i + 2 * U, wn);
+                add(b, std::false_type{});
+            }
+        }
+    } else {
+        uint32_t i = 0;
+        for (; i + U <= nmin; i += U) {
+            Batch b;
+            issue(b, cs + 1 + i, wn);
+            fetch(cs + 1 + i + U, wn);
+            add(b, std::true_type{});
+        }
+        for (; i < nmax; i += U) {
+            Batch b;
+            issue(b, cs + 1 + i, wn);
+            fetch(cs + 1 + i + U, wn);
+            add(b, std::false_type{});
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+#pragma unroll
+        for (int q = 0; q < CPL; ++q) acc[c][q] = fmaf(p[c][q], mrow[c][q], acc[c][q]);
+        if (live) store_vec<CPL>(dst[c], acc[c]);
+    }
+}
+
+template <typename T, int CPL, int G, int NCH>
 __global__ __launch_bounds__(kBlock) MTTKRP_OCCUPANCY void k_mttkrp(
     const uint2 *__restrict__ st, const uint32_t *__restrict__ cstart, uint32_t nchunk,
     const T *__restrict__ Fleaf, const T *__restrict__ Fmid, int R, float *__restrict__ out,
     float *__restrict__ carry) {
-    const int lane = threadIdx.x % G;
-    const GlobalRows<T, CPL, NCH, SMALL> src(Fleaf, Fmid, R, G, lane);
-    mttkrp_chunk<T, CPL, G, NCH, SMALL>(st, cstart, nchunk, src, R, out, carry,
-                                        (blockIdx.x * (uint32_t)kBlock + threadIdx.x) / G, lane);
+    mttkrp_group_chunk<T, CPL, G, NCH>(st, cstart, nchunk, Fleaf, Fmid, R, out, carry,
+                                       (blockIdx.x * (uint32_t)kBlock + threadIdx.x) / G,
+                                       threadIdx.x % G);
 }
 
 template <typename T, int CPL, int G, int NCH, bool SMALL>
@@ -515,9 +795,9 @@ __global__ __launch_bounds__(kBlock) void k_mttkrp_res(
     float *__restrict__ out, float *__restrict__ carry) {
     const int lane = threadIdx.x % G;
     const GlobalRows<T, CPL, NCH, SMALL> src(Fleaf, Fmid, R, G, lane);
-    mttkrp_chunk<T, CPL, G, NCH, SMALL, true>(st, cstart, nchunk, src, R, out, carry,
-                                              (blockIdx.x * (uint32_t)kBlock + threadIdx.x) / G,
-                                              lane, Froot);
+    mttkrp_res_chunk<T, CPL, G, NCH, SMALL>(st, cstart, nchunk, src, R, out, carry,
+                                            (blockIdx.x * (uint32_t)kBlock + threadIdx.x) / G,
+                                            lane, Froot);
 }
 
 // Grouped MTTKRP over many tensors of one kernel shape: a persistent grid
@@ -526,31 +806,19 @@ __global__ __launch_bounds__(kBlock) void k_mttkrp_res(
 // gridDim.x, ...; each lane group takes kper consecutive chunks of its item
 // in turn.  Every chunk writes its own rows and carry, so the grid, the
 // shape and kper change no result.
-template <typename T, int CPL, int G, int NCH, bool SMALL>
+template <typename T, int CPL, int G, int NCH>
 __global__ __launch_bounds__(kBlock) MTTKRP_OCCUPANCY void k_mttkrp_group(
     const GroupMttkrp *__restrict__ desc, const uint2 *__restrict__ items, uint32_t nitems,
     uint32_t kper) {
     const int lane = threadIdx.x % G;
-    if (kper == 1) {  // the common form, without the inner loop
-        for (uint32_t it = blockIdx.x; it < nitems; it += gridDim.x) {
-            const uint2 w = items[it];
-            const GroupMttkrp &d = desc[w.x];
-            const GlobalRows<T, CPL, NCH, SMALL> src((const T *)d.Fleaf, (const T *)d.Fmid, d.R,
-                                                     G, lane);
-            mttkrp_chunk<T, CPL, G, NCH, SMALL>(d.stream, d.chunk_start, d.nchunk, src, d.R,
-                                                d.out, d.carry, w.y + threadIdx.x / G, lane);
-        }
-        return;
-    }
     const uint32_t first = (threadIdx.x / G) * kper;
     for (uint32_t it = blockIdx.x; it < nitems; it += gridDim.x) {
         const uint2 w = items[it];
         const GroupMttkrp &d = desc[w.x];
-        const GlobalRows<T, CPL, NCH, SMALL> src((const T *)d.Fleaf, (const T *)d.Fmid, d.R, G,
-                                                 lane);
         for (uint32_t q = 0; q < kper; ++q)
-            mttkrp_chunk<T, CPL, G, NCH, SMALL>(d.stream, d.chunk_start, d.nchunk, src, d.R,
-                                                d.out, d.carry, w.y + first + q, lane);
+            mttkrp_group_chunk<T, CPL, G, NCH>(d.stream, d.chunk_start, d.nchunk,
+                                               (const T *)d.Fleaf, (const T *)d.Fmid, d.R, d.out,
+                                               d.carry, w.y + first + q, lane);
     }
 }
 
@@ -613,7 +881,7 @@ __global__ __launch_bounds__(kBlock) MTTKRP_OCCUPANCY void k_gather_probe(
             lds_rows[x] = Fleaf[(uint32_t)x % nfill];
         __syncthreads();
     }
-    constexpr bool kShare = G <= 32 && DFACTO_SHARE_ENTRIES;
+    constexpr bool kShare = G <= 32;
     constexpr int KL = kShare ? (kUnroll + G - 1) / G : kUnroll;
     auto load_batch = [&](uint32_t at, uint2 (&wl)[KL]) {
 #pragma unroll
@@ -991,13 +1259,35 @@ struct Tables {
     int64_t rows_out = 0;
 };
 
-template <typename T, int CPL, int G, int NCH>
+// The lane groups of the main kernel, from the fix-ups' shape `sh` (which sets
+// the order of the carries' sums and so stays as it is).  Microseconds for
+// three modes; "a x b": b lanes of a columns:
+//  * at least five lanes per row: with fewer a wave holds more groups, and
+//    nearly every entry finds one of them storing a row.  50M nonzeros, FP32:
+//    R = 8 1x8 1799 against 4x2 2310; R = 16 2x8 1885 against 4x4 2112.
+//  * BF16 rows of at most eight lanes: two columns per lane (a 4-byte load),
+//    half the registers per row and so more rows in flight.  R = 32, 50M:
+//    2x16 1905 against 4x8 1976; 100M relabeled 2950 against 3071 (8x4: 3085).
+//  * the same for FP32 while the chunks are too few to fill the device with
+//    eight-lane groups: R = 32, 1M nonzeros 185 against 273, 3M (8500 chunks)
+//    240 against 296, but 10M (28,000 chunks) 557 against 510.
+MttkrpShape main_shape(MttkrpShape sh, int R, dfacto_dtype dtype, int64_t nchunk, int num_cu) {
+    if (sh.nch != 1) return sh;
+    while (sh.cpl > 1 && (R + sh.cpl - 1) / sh.cpl <= 4) sh.cpl /= 2;
+    if (sh.cpl == 4 && (R + 3) / 4 <= 8 && (dtype == DFACTO_BF16 || nchunk < 48 * (int64_t)num_cu))
+        sh.cpl = 2;
+    const int lanes = (R + sh.cpl - 1) / sh.cpl;
+    sh.g = 2;
+    while (sh.g < lanes) sh.g <<= 1;
+    return sh;
+}
+
 // fix/ev: when set, the carry fix-ups go to stream `fix`, ordered after the
 // main kernel by `ev` recorded on ctx's stream; carry_in: the carries' buffer
-// (else the context's carry workspace)
-void run(dfacto_ctx *ctx, const ModeData &md, int R, const Tables &tb, float *out, bool small,
-         const void *Froot = nullptr, float *carry_in = nullptr, hipStream_t fix = nullptr,
-         hipEvent_t ev = nullptr) {
+// (else the context's carry workspace); sh: the fix-ups' shape
+void run(dfacto_ctx *ctx, const ModeData &md, int R, dfacto_dtype dtype, const MttkrpShape &sh,
+         const Tables &tb, float *out, bool small, const void *Froot = nullptr,
+         float *carry_in = nullptr, hipStream_t fix = nullptr, hipEvent_t ev = nullptr) {
     hipStream_t s = ctx->stream;
     const uint32_t nchunk = (uint32_t)md.nchunk;
     float *const out_user = out;
@@ -1010,31 +1300,33 @@ void run(dfacto_ctx *ctx, const ModeData &md, int R, const Tables &tb, float *ou
                             : (float *)ws_get(ctx, dfacto_ctx::kCarry,
                                               sizeof(float) *
                                                   (size_t)std::max<int64_t>(md.nchunk, 1) * R);
-    const T *Fleaf = (const T *)tb.leaf, *Fmid = (const T *)tb.mid;
-    constexpr int gpb = kBlock / G;  // groups per block
-    if (nchunk > 0) {
-        const unsigned blocks = (nchunk + gpb - 1) / gpb;
-        if (Froot) {
-            if (small)
-                hipLaunchKernelGGL((k_mttkrp_res<T, CPL, G, NCH, true>), dim3(blocks),
-                                   dim3(kBlock), 0, s, md.stream, md.chunk_start, nchunk, Fleaf,
-                                   Fmid, (const T *)Froot, R, out, carry);
-            else
-                hipLaunchKernelGGL((k_mttkrp_res<T, CPL, G, NCH, false>), dim3(blocks),
-                                   dim3(kBlock), 0, s, md.stream, md.chunk_start, nchunk, Fleaf,
-                                   Fmid, (const T *)Froot, R, out, carry);
-        } else {
-            prof_mark(ctx);
-            if (small)
-                hipLaunchKernelGGL((k_mttkrp<T, CPL, G, NCH, true>), dim3(blocks), dim3(kBlock),
-                                   0, s, md.stream, md.chunk_start, nchunk, Fleaf, Fmid, R, out,
-                                   carry);
-            else
-                hipLaunchKernelGGL((k_mttkrp<T, CPL, G, NCH, false>), dim3(blocks), dim3(kBlock),
-                                   0, s, md.stream, md.chunk_start, nchunk, Fleaf, Fmid, R, out,
-                                   carry);
-            prof_mark(ctx);
-        }
+    if (nchunk > 0 && Froot) {
+        with_shape(dtype, sh, [&](auto tc, auto cplc, auto gc, auto nchc) {
+            using T = typename decltype(tc)::type;
+            constexpr int CPL = decltype(cplc)::value, G = decltype(gc)::value,
+                          NCH = decltype(nchc)::value;
+            const unsigned blocks = (nchunk + kBlock / G - 1) / (kBlock / G);
+            auto go = [&](auto kern) {
+                hipLaunchKernelGGL(kern, dim3(blocks), dim3(kBlock), 0, s, md.stream,
+                                   md.chunk_start, nchunk, (const T *)tb.leaf,
+                                   (const T *)tb.mid, (const T *)Froot, R, out, carry);
+            };
+            if (small) go(k_mttkrp_res<T, CPL, G, NCH, true>);
+            else go(k_mttkrp_res<T, CPL, G, NCH, false>);
+        });
+    } else if (nchunk > 0) {
+        prof_mark(ctx);
+        const MttkrpShape ms = main_shape(sh, R, dtype, md.nchunk, ctx->num_cu);
+        with_shape(dtype, ms, [&](auto tc, auto cplc, auto gc, auto nchc) {
+            using T = typename decltype(tc)::type;
+            constexpr int CPL = decltype(cplc)::value, G = decltype(gc)::value,
+                          NCH = decltype(nchc)::value;
+            const unsigned blocks = (nchunk + kBlock / G - 1) / (kBlock / G);
+            hipLaunchKernelGGL((k_mttkrp<T, CPL, G, NCH>), dim3(blocks), dim3(kBlock), 0, s,
+                               md.stream, md.chunk_start, nchunk, (const T *)tb.leaf,
+                               (const T *)tb.mid, R, out, carry);
+        });
+        prof_mark(ctx);
     }
     if (fix) {
         DF_HIP(hipEventRecord(ev, s));
@@ -1044,13 +1336,17 @@ void run(dfacto_ctx *ctx, const ModeData &md, int R, const Tables &tb, float *ou
     const uint32_t nempty = (uint32_t)md.nempty;
     const uint32_t egroups = nempty == 0 ? 0u : std::min<uint32_t>(nempty, 65536u);
     const uint64_t groups = (uint64_t)md.nruns_short + egroups;
-    constexpr int gpl = kLongBlock / G;  // lane groups per fix-up block
-    const uint64_t fblocks = (uint64_t)md.nruns_long + (groups + gpl - 1) / gpl;
-    if (fblocks > 0)
-        hipLaunchKernelGGL((k_fix<CPL, G, NCH>), dim3((unsigned)fblocks), dim3(kLongBlock), 0, s,
-                           md.runs_long, (uint32_t)md.nruns_long, md.runs_short,
-                           (uint32_t)md.nruns_short, carry, R, out, md.empty_rows, nempty,
-                           egroups);
+    with_shape(DFACTO_F32, sh, [&](auto, auto cplc, auto gc, auto nchc) {
+        constexpr int CPL = decltype(cplc)::value, G = decltype(gc)::value,
+                      NCH = decltype(nchc)::value;
+        constexpr int gpl = kLongBlock / G;  // lane groups per fix-up block
+        const uint64_t fblocks = (uint64_t)md.nruns_long + (groups + gpl - 1) / gpl;
+        if (fblocks > 0)
+            hipLaunchKernelGGL((k_fix<CPL, G, NCH>), dim3((unsigned)fblocks), dim3(kLongBlock), 0,
+                               s, md.runs_long, (uint32_t)md.nruns_long, md.runs_short,
+                               (uint32_t)md.nruns_short, carry, R, out, md.empty_rows, nempty,
+                               egroups);
+    });
     if (tb.pad_out && tb.rows_out > 0) {
         int log2S = 0;
         while ((1 << log2S) < tb.stride) ++log2S;
@@ -1281,11 +1577,7 @@ void launch_mttkrp(dfacto_ctx *ctx, const dfacto_tensor *t, int mode, int R, dfa
     const MttkrpShape sh =
         tb.pad_out ? mttkrp_shape(tb.stride, dtype, tb.leaf, tb.mid, tb.pad_out, true)
                    : mttkrp_shape(R, dtype, Fleaf, Fmid, out, md.perm_leaf != nullptr);
-    with_shape(dtype, sh, [&](auto tc, auto cplc, auto gc, auto nchc) {
-        using T = typename decltype(tc)::type;
-        run<T, decltype(cplc)::value, decltype(gc)::value, decltype(nchc)::value>(ctx, md, R, tb,
-                                                                                 out, sm);
-    });
+    run(ctx, md, R, dtype, sh, tb, out, sm);
 }
 
 size_t mttkrp_buffers(const dfacto_tensor *t, int mode, int R, dfacto_dtype dtype,
@@ -1305,12 +1597,7 @@ void launch_mttkrp_in(dfacto_ctx *ctx, const dfacto_tensor *t, int mode, int R,
     const MttkrpShape sh = mttkrp_shape(R, dtype, Fleaf, Fmid, out, md.perm_leaf != nullptr);
     const bool sm = mttkrp_small(t, mode);
     const Tables tb = gather_tables(ctx, t, mode, R, dtype, Fleaf, Fmid, perm);
-    with_shape(dtype, sh, [&](auto tc, auto cplc, auto gc, auto nchc) {
-        using T = typename decltype(tc)::type;
-        run<T, decltype(cplc)::value, decltype(gc)::value, decltype(nchc)::value>(ctx, md, R, tb,
-                                                                                 out, sm, nullptr,
-                                                                                 carry);
-    });
+    run(ctx, md, R, dtype, sh, tb, out, sm, nullptr, carry);
 }
 
 void launch_mttkrp_split(dfacto_ctx *ctx, const dfacto_tensor *t, int mode, int R,
@@ -1329,11 +1616,7 @@ void launch_mttkrp_split(dfacto_ctx *ctx, const dfacto_tensor *t, int mode, int 
     const MttkrpShape sh =
         tb.pad_out ? mttkrp_shape(tb.stride, dtype, tb.leaf, tb.mid, tb.pad_out, true)
                    : mttkrp_shape(R, dtype, Fleaf, Fmid, out, md.perm_leaf != nullptr);
-    with_shape(dtype, sh, [&](auto tc, auto cplc, auto gc, auto nchc) {
-        using T = typename decltype(tc)::type;
-        run<T, decltype(cplc)::value, decltype(gc)::value, decltype(nchc)::value>(
-            ctx, md, R, tb, out, sm, nullptr, carry, fix, ev);
-    });
+    run(ctx, md, R, dtype, sh, tb, out, sm, nullptr, carry, fix, ev);
 }
 
 void launch_mttkrp_resid(dfacto_ctx *ctx, const dfacto_tensor *t, int mode, int R,
@@ -1346,18 +1629,16 @@ void launch_mttkrp_resid(dfacto_ctx *ctx, const dfacto_tensor *t, int mode, int 
     if (sr.cpl < sh.cpl) sh = sr;
     const bool sm = mttkrp_small(t, mode);
     const Tables tb = gather_tables(ctx, t, mode, R, dtype, Fleaf, Fmid);
-    with_shape(dtype, sh, [&](auto tc, auto cplc, auto gc, auto nchc) {
-        using T = typename decltype(tc)::type;
-        run<T, decltype(cplc)::value, decltype(gc)::value, decltype(nchc)::value>(ctx, md, R, tb,
-                                                                                 out, sm, Froot);
-    });
+    run(ctx, md, R, dtype, sh, tb, out, sm, Froot);
 }
 
 void launch_gather_probe(dfacto_ctx *ctx, const dfacto_tensor *t, int mode, int R,
                          dfacto_dtype dtype, const void *Fleaf, const void *Fmid, int pattern,
                          float *sink) {
     const ModeData &md = t->mode[mode];
-    const MttkrpShape sh = mttkrp_shape(R, dtype, Fleaf, Fmid, sink, md.perm_leaf != nullptr);
+    const MttkrpShape sh =
+        main_shape(mttkrp_shape(R, dtype, Fleaf, Fmid, sink, md.perm_leaf != nullptr), R, dtype,
+                   md.nchunk, ctx->num_cu);
     if (sh.nch != 1) throw Error{DFACTO_E_UNSUPPORTED, "the gather probe takes R <= 64 * CPL"};
     if ((pattern == 5 || pattern >= 8) && R > kProbeLdsRowElems)
         throw Error{DFACTO_E_UNSUPPORTED, "the LDS patterns take R <= 64"};
@@ -1404,26 +1685,26 @@ void launch_gather_probe(dfacto_ctx *ctx, const dfacto_tensor *t, int mode, int 
     DF_LAUNCHED();
 }
 
+MttkrpShape mttkrp_main_shape(const dfacto_ctx *ctx, const MttkrpShape &sh, int R,
+                              dfacto_dtype dtype, int64_t nchunk) {
+    return main_shape(sh, R, dtype, nchunk, ctx->num_cu);
+}
+
 unsigned mttkrp_group_chunks_per_item(const MttkrpShape &sh, unsigned kper) {
     return (unsigned)(kBlock / sh.g) * kper;
 }
 
-void launch_mttkrp_group(dfacto_ctx *ctx, dfacto_dtype dtype, const MttkrpShape &sh, bool small,
+void launch_mttkrp_group(dfacto_ctx *ctx, dfacto_dtype dtype, const MttkrpShape &sh,
                          const GroupMttkrp *d_desc, const uint2 *d_items, uint32_t nitems,
                          unsigned grid, unsigned kper) {
     if (nitems == 0) return;
     if (kper < 1 || grid < 1) throw Error{DFACTO_E_INVALID, "grouped MTTKRP launch shape"};
-    hipStream_t s = ctx->stream;
     with_shape(dtype, sh, [&](auto tc, auto cplc, auto gc, auto nchc) {
         using T = typename decltype(tc)::type;
-        constexpr int CPL = decltype(cplc)::value, G = decltype(gc)::value,
-                      NCH = decltype(nchc)::value;
-        if (small)
-            hipLaunchKernelGGL((k_mttkrp_group<T, CPL, G, NCH, true>), dim3(grid), dim3(kBlock), 0,
-                               s, d_desc, d_items, nitems, kper);
-        else
-            hipLaunchKernelGGL((k_mttkrp_group<T, CPL, G, NCH, false>), dim3(grid), dim3(kBlock),
-                               0, s, d_desc, d_items, nitems, kper);
+        hipLaunchKernelGGL((k_mttkrp_group<T, decltype(cplc)::value, decltype(gc)::value,
+                                           decltype(nchc)::value>),
+                           dim3(grid), dim3(kBlock), 0, ctx->stream, d_desc, d_items, nitems,
+                           kper);
     });
     DF_LAUNCHED();
 }
