@@ -208,6 +208,22 @@ __device__ __forceinline__ void store_vec(DF_GLOBAL float *p, const float (&v)[C
     }
 }
 
+// CPL consecutive floats of LDS
+template <int CPL>
+__device__ __forceinline__ void store_lds(float *p, const float (&v)[CPL]) {
+    if constexpr (CPL == 2) *reinterpret_cast<float2 *>(p) = make_float2(v[0], v[1]);
+    else p[0] = v[0];
+}
+template <int CPL>
+__device__ __forceinline__ void load_lds(const float *p, float (&v)[CPL]) {
+    if constexpr (CPL == 2) {
+        const float2 x = *reinterpret_cast<const float2 *>(p);
+        v[0] = x.x; v[1] = x.y;
+    } else {
+        v[0] = p[0];
+    }
+}
+
 template <int CPL>
 __device__ __forceinline__ void load_f32(const DF_GLOBAL float *p, float (&v)[CPL]) {
     RowLoad<float, CPL>::load(p, v);
@@ -788,6 +804,154 @@ __global__ __launch_bounds__(kBlock) MTTKRP_OCCUPANCY void k_mttkrp(
                                        threadIdx.x % G);
 }
 
+// ---- one block per chunk ---------------------------------------------------
+// For tensors with too few chunks to fill the device with lane groups: a
+// lane group walks its chunk's 512 entries one batch after another, so a call
+// on a small tensor lasts as long as that walk's memory round trips (65 us),
+// however little there is to do.  Here a block takes one chunk and W = CPL * G
+// columns; Algorithm 1's two stages run one after the other, each spread over
+// the block's lane groups:
+//   stage 1: a group forms the P of the fibers whose headers lie in its share
+//     of the entries, all their leaf rows in flight at once, and leaves P and
+//     the mid row in LDS;
+//   stage 2: a group adds P * mid row over the fibers of whole output rows.
+// Every fiber's and every row's sum runs in stream order, so the result is
+// bitwise that of mttkrp_group_chunk.
+constexpr int kBlkEntries = 640;  // a chunk of chunk_len <= 512: one more segment at most
+constexpr int kBlkFibers = kBlkEntries / 2;
+static_assert(kBlkEntries >= DFACTO_CHUNK_DEFAULT + kFiberCap, "a chunk fits the block's LDS");
+
+template <typename T, int CPL, int G>
+__global__ __launch_bounds__(kBlock) void k_mttkrp_block(
+    const uint2 *__restrict__ st_, const uint32_t *__restrict__ cstart,
+    const T *__restrict__ Fleaf, const T *__restrict__ Fmid, int R, float *__restrict__ out_,
+    float *__restrict__ carry_) {
+    constexpr int W = CPL * G, NG = kBlock / G, U = 16;
+    constexpr int kWords = kBlkEntries / 64, kFWords = kBlkFibers / 64;
+    __shared__ uint2 ent[kBlkEntries];
+    __shared__ alignas(16) float Ps[kBlkFibers * W], Ms[kBlkFibers * W];
+    __shared__ uint32_t frow[kBlkFibers];               // the row of each segment's header
+    __shared__ uint64_t hmask[kWords], rmask[kFWords];  // headers; segments that open a row
+    __shared__ int before[kWords + 1];                  // headers before each word of hmask
+    const DF_GLOBAL uint2 *__restrict__ st = gptr(st_);
+    const uint32_t gid = blockIdx.x, cs = gptr(cstart)[gid];
+    const int L = (int)min(gptr(cstart)[gid + 1] - cs, (uint32_t)kBlkEntries);
+    if (L <= 0) return;
+    const int tid = threadIdx.x, g = tid / G, lane = tid % G;
+
+    if (tid < kFWords) rmask[tid] = 0;
+    for (int i = tid; i < kBlkEntries; i += kBlock) {
+        const uint2 w = i < L ? load_entry(st + cs + i) : make_uint2(0u, 0u);
+        ent[i] = w;
+        const uint64_t m = __ballot((int32_t)w.x < 0);
+        if (tid % 64 == 0) hmask[i / 64] = m;
+    }
+    __syncthreads();
+    if (tid <= kWords) {
+        int n = 0;
+        for (int w = 0; w < tid; ++w) n += __popcll(hmask[w]);
+        before[tid] = n;
+    }
+    // the first header from entry b on (L: none), and the headers before b
+    auto next_head = [&](int b) {
+        int w = b >> 6;
+        if (b >= L) return L;
+        uint64_t m = hmask[w] & (~0ull << (b & 63));
+        while (!m && ++w < kWords) m = hmask[w];
+        return m ? 64 * w + __ffsll((unsigned long long)m) - 1 : L;
+    };
+    auto heads_before = [&](int b) {
+        return b >= L ? before[kWords]
+                      : before[b >> 6] + __popcll(hmask[b >> 6] & ~(~0ull << (b & 63)));
+    };
+    const int share = (L + NG - 1) / NG;
+    const int beg = next_head(g * share), end = next_head((g + 1) * share);
+    __syncthreads();
+    const int nf = before[kWords], f0 = heads_before(g * share);
+
+    // stage 1
+    const int c0 = blockIdx.y * W + lane * CPL;
+    const uint32_t colb = (uint32_t)(c0 < R ? c0 : blockIdx.y * W) * (uint32_t)sizeof(T);
+    const uint32_t rowb = (uint32_t)R * (uint32_t)sizeof(T);
+    const uint64_t leaf0 = (uint64_t)(uintptr_t)Fleaf + colb, mid0 = (uint64_t)(uintptr_t)Fmid + colb;
+    {
+        float *ps = Ps + (f0 - 1) * W + lane * CPL, *ms = Ms + (f0 - 1) * W + lane * CPL;
+        int f = f0 - 1;
+        float p[CPL];
+#pragma unroll
+        for (int q = 0; q < CPL; ++q) p[q] = 0.f;
+        for (int at = beg; at < end; at += U) {
+            uint2 w[U];
+            float r[U][CPL];
+#pragma unroll
+            for (int u = 0; u < U; ++u) w[u] = ent[min(at + u, end - 1)];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                RowLoad<T, CPL>::load(
+                    (const DF_GLOBAL T *)(uintptr_t)(((int32_t)w[u].x < 0 ? mid0 : leaf0) +
+                                                     (uint64_t)(w[u].x & kIdxMask) * rowb),
+                    r[u]);
+            static_for<0, U>([&](auto uc) {
+                constexpr int u = decltype(uc)::value;
+                if (at + u >= end) return;
+                if ((int32_t)w[u].x < 0) {
+                    if (f >= f0) store_lds<CPL>(ps, p);
+                    ++f;
+                    ps += W;
+                    ms += W;
+                    store_lds<CPL>(ms, r[u]);
+                    if (lane == 0) {
+                        frow[f] = w[u].y;
+                        if (w[u].x & kRootBit) atomicOr((uint32_t *)rmask + (f >> 5), 1u << (f & 31));
+                    }
+                    // 0, or NaN for an Inf or NaN in the mid row, as the lane
+                    // groups have it for all but a chunk's first segment
+#pragma unroll
+                    for (int q = 0; q < CPL; ++q) p[q] = f ? fmaf(0.f, r[u][q], 0.f) : 0.f;
+                } else {
+#pragma unroll
+                    for (int q = 0; q < CPL; ++q)
+                        p[q] = fmaf(__uint_as_float(w[u].y), r[u][q], p[q]);
+                }
+            });
+        }
+        if (f >= f0) store_lds<CPL>(ps, p);
+    }
+    __syncthreads();
+
+    // stage 2: the rows that open in the group's share of the segments (and,
+    // group 0, the row that the chunk begins in)
+    auto next_row = [&](int f) {  // the first segment from f on that opens a row
+        if (f >= nf) return nf;
+        int w = f >> 6;
+        uint64_t m = rmask[w] & (~0ull << (f & 63));
+        while (!m && ++w < kFWords) m = rmask[w];
+        return m ? 64 * w + __ffsll((unsigned long long)m) - 1 : nf;
+    };
+    const int fshare = (nf + NG - 1) / NG;
+    const int stop = next_row((g + 1) * fshare);
+    DF_GLOBAL float *out = gptr(out_), *carry = gptr(carry_);
+    for (int f = g == 0 ? 0 : next_row(g * fshare); f < stop;) {
+        const bool opens = (rmask[f >> 6] >> (f & 63)) & 1;
+        const uint32_t row = frow[f];
+        const int e = next_row(f + 1);
+        float acc[CPL];
+#pragma unroll
+        for (int q = 0; q < CPL; ++q) acc[q] = 0.f;
+        const float *ps = Ps + f * W + lane * CPL, *ms = Ms + f * W + lane * CPL;
+#pragma unroll 4
+        for (; f < e; ++f, ps += W, ms += W) {
+            float p[CPL], m[CPL];
+            load_lds<CPL>(ps, p);
+            load_lds<CPL>(ms, m);
+#pragma unroll
+            for (int q = 0; q < CPL; ++q) acc[q] = fmaf(p[q], m[q], acc[q]);
+        }
+        if (c0 < R)
+            store_vec<CPL>((opens ? out + (size_t)row * R : carry + (size_t)gid * R) + c0, acc);
+    }
+}
+
 template <typename T, int CPL, int G, int NCH, bool SMALL>
 __global__ __launch_bounds__(kBlock) void k_mttkrp_res(
     const uint2 *__restrict__ st, const uint32_t *__restrict__ cstart, uint32_t nchunk,
@@ -1259,6 +1423,36 @@ struct Tables {
     int64_t rows_out = 0;
 };
 
+// The block-per-chunk kernel where it is the faster one (false: not launched).
+// Its time grows by about 10 ns per block (8 columns; 14 ns for 16) from 11 us,
+// while the lane groups take 60-75 us however few chunks there are, until
+// about 6000 chunks fill the device.  Three modes of 20,000 nonzeros, R = 8:
+// 33 us against 141 (200 before either); 1M nonzeros (3902 chunks per mode),
+// R = 8 119 against 195, R = 16 170 against 193, but R = 32 (two slices) 290
+// against 185; 3M (8500 chunks), R = 8 314 against 216.
+bool launch_block(dfacto_ctx *ctx, const ModeData &md, int R, dfacto_dtype dtype,
+                  const MttkrpShape &sh, const Tables &tb, float *out, float *carry) {
+    if (md.chunk_len > DFACTO_CHUNK_DEFAULT) return false;
+    const bool even = sh.cpl >= 2, narrow = R <= 8;
+    const unsigned slices = narrow ? 1u : (unsigned)(R + 15) / 16;
+    if ((uint64_t)md.nchunk * slices > (uint64_t)(narrow ? 20 : 16) * ctx->num_cu) return false;
+    auto go = [&](auto tc, auto cplc, auto gc) {
+        using T = typename decltype(tc)::type;
+        hipLaunchKernelGGL((k_mttkrp_block<T, decltype(cplc)::value, decltype(gc)::value>),
+                           dim3((unsigned)md.nchunk, slices), dim3(kBlock), 0, ctx->stream,
+                           md.stream, md.chunk_start, (const T *)tb.leaf, (const T *)tb.mid, R,
+                           out, carry);
+    };
+    auto by_type = [&](auto tc) {
+        if (narrow) go(tc, IntC<1>{}, IntC<8>{});
+        else if (even) go(tc, IntC<2>{}, IntC<8>{});
+        else go(tc, IntC<1>{}, IntC<16>{});
+    };
+    if (dtype == DFACTO_F32) by_type(TypeC<float>{});
+    else by_type(TypeC<uint16_t>{});
+    return true;
+}
+
 // The lane groups of the main kernel, from the fix-ups' shape `sh` (which sets
 // the order of the carries' sums and so stays as it is).  Microseconds for
 // three modes; "a x b": b lanes of a columns:
@@ -1317,15 +1511,16 @@ void run(dfacto_ctx *ctx, const ModeData &md, int R, dfacto_dtype dtype, const M
     } else if (nchunk > 0) {
         prof_mark(ctx);
         const MttkrpShape ms = main_shape(sh, R, dtype, md.nchunk, ctx->num_cu);
-        with_shape(dtype, ms, [&](auto tc, auto cplc, auto gc, auto nchc) {
-            using T = typename decltype(tc)::type;
-            constexpr int CPL = decltype(cplc)::value, G = decltype(gc)::value,
-                          NCH = decltype(nchc)::value;
-            const unsigned blocks = (nchunk + kBlock / G - 1) / (kBlock / G);
-            hipLaunchKernelGGL((k_mttkrp<T, CPL, G, NCH>), dim3(blocks), dim3(kBlock), 0, s,
-                               md.stream, md.chunk_start, nchunk, (const T *)tb.leaf,
-                               (const T *)tb.mid, R, out, carry);
-        });
+        if (!launch_block(ctx, md, R, dtype, sh, tb, out, carry))
+            with_shape(dtype, ms, [&](auto tc, auto cplc, auto gc, auto nchc) {
+                using T = typename decltype(tc)::type;
+                constexpr int CPL = decltype(cplc)::value, G = decltype(gc)::value,
+                              NCH = decltype(nchc)::value;
+                const unsigned blocks = (nchunk + kBlock / G - 1) / (kBlock / G);
+                hipLaunchKernelGGL((k_mttkrp<T, CPL, G, NCH>), dim3(blocks), dim3(kBlock), 0, s,
+                                   md.stream, md.chunk_start, nchunk, (const T *)tb.leaf,
+                                   (const T *)tb.mid, R, out, carry);
+            });
         prof_mark(ctx);
     }
     if (fix) {
