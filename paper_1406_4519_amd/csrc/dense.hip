@@ -39,6 +39,15 @@ __device__ __forceinline__ double ld<uint16_t>(const uint16_t *p, int64_t i) {
     return (double)__uint_as_float((uint32_t)p[i] << 16);
 }
 
+template <typename T>
+__device__ __forceinline__ float ldf(const T *p, int64_t i);
+template <>
+__device__ __forceinline__ float ldf<float>(const float *p, int64_t i) { return p[i]; }
+template <>
+__device__ __forceinline__ float ldf<uint16_t>(const uint16_t *p, int64_t i) {
+    return __uint_as_float((uint32_t)p[i] << 16);
+}
+
 __device__ __forceinline__ uint16_t f32_to_bf16(float f) {
     uint32_t b = __float_as_uint(f);
     if ((b & 0x7F800000u) == 0x7F800000u) return (uint16_t)((b >> 16) | ((b & 0xFFFFu) ? 0x40u : 0u));
@@ -57,99 +66,10 @@ __device__ __forceinline__ void st_out<uint16_t>(uint16_t *p, int64_t i, double 
     p[i] = f32_to_bf16((float)v);
 }
 
-// 8 consecutive entries p[base + c0 .. + 8) widened to double; entries at
-// columns >= R read as 0.  Vector loads when the row layout allows.
-// `vec` (computed on the host) says the rows allow 16-byte loads: R is a
-// multiple of 4 (FP32) or 8 (BF16) and the base pointer is 16-byte aligned.
-template <typename T>
-__device__ __forceinline__ void load8(const T *p, int64_t base, int c0, int R, bool vec,
-                                      double (&v)[8]);
-template <>
-__device__ __forceinline__ void load8<float>(const float *p, int64_t base, int c0, int R, bool vec,
-                                             double (&v)[8]) {
-    if (vec && c0 + 8 <= R) {
-        const float4 a = *reinterpret_cast<const float4 *>(p + base + c0);
-        const float4 b = *reinterpret_cast<const float4 *>(p + base + c0 + 4);
-        v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-        v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-    } else {
-#pragma unroll
-        for (int q = 0; q < 8; ++q) v[q] = (c0 + q < R) ? (double)p[base + c0 + q] : 0.0;
-    }
-}
-template <>
-__device__ __forceinline__ void load8<uint16_t>(const uint16_t *p, int64_t base, int c0, int R,
-                                                bool vec, double (&v)[8]) {
-    if (vec && c0 + 8 <= R) {
-        const uint4 a = *reinterpret_cast<const uint4 *>(p + base + c0);
-        const uint32_t w[4] = {a.x, a.y, a.z, a.w};
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            v[2 * q] = (double)__uint_as_float(w[q] << 16);
-            v[2 * q + 1] = (double)__uint_as_float(w[q] & 0xFFFF0000u);
-        }
-    } else {
-#pragma unroll
-        for (int q = 0; q < 8; ++q)
-            v[q] = (c0 + q < R) ? (double)__uint_as_float((uint32_t)p[base + c0 + q] << 16) : 0.0;
-    }
-}
-
 // ---------------------------------------------------------------------------
-// Gram: part[b][r][s] = sum over the rows visited by block b of F[row][r] F[row][s]
-// grid.x: row blocks, grid.y: TSxTS output tiles.  A tile is covered by
-// (TS/8)^2 threads with 8x8 register tiles; the block holds kBlock/(TS/8)^2
-// slices of rows, combined in slice order through LDS.
+// Gram: part[b][r][s] = sum over the rows visited by block b of F[row][r] F[row][s],
+// then a fixed-order reduction over the blocks.
 // ---------------------------------------------------------------------------
-template <typename T, int TS>
-__global__ __launch_bounds__(kBlock) void k_gram_partial(const T *__restrict__ F, int64_t rows,
-                                                         int R, int vec, double *__restrict__ part) {
-    constexpr int TT = TS / 8;
-    constexpr int TPT = TT * TT;
-    constexpr int SL = kBlock / TPT;
-    __shared__ double tile[TS * TS];
-    const int nt = (R + TS - 1) / TS;
-    const int rt = blockIdx.y / nt, ct = blockIdx.y % nt;
-    const int slice = threadIdx.x / TPT, t = threadIdx.x % TPT;
-    const int ty = t / TT, tx = t % TT;
-    const int ra = rt * TS + ty * 8, cb = ct * TS + tx * 8;
-    double acc[8][8];
-#pragma unroll
-    for (int a = 0; a < 8; ++a)
-#pragma unroll
-        for (int b = 0; b < 8; ++b) acc[a][b] = 0.0;
-    const bool active = ra < R && cb < R;
-    if (active) {
-        for (int64_t row = (int64_t)blockIdx.x * SL + slice; row < rows;
-             row += (int64_t)gridDim.x * SL) {
-            double x[8], y[8];
-            load8<T>(F, row * R, ra, R, vec, x);
-            load8<T>(F, row * R, cb, R, vec, y);
-#pragma unroll
-            for (int a = 0; a < 8; ++a)
-#pragma unroll
-                for (int b = 0; b < 8; ++b) acc[a][b] = fma(x[a], y[b], acc[a][b]);
-        }
-    }
-    for (int s = 0; s < SL; ++s) {
-        __syncthreads();
-        if (slice == s) {
-#pragma unroll
-            for (int a = 0; a < 8; ++a)
-#pragma unroll
-                for (int b = 0; b < 8; ++b) {
-                    const int e = (ty * 8 + a) * TS + tx * 8 + b;
-                    tile[e] = (s == 0) ? acc[a][b] : tile[e] + acc[a][b];
-                }
-        }
-    }
-    __syncthreads();
-    double *pb = part + (size_t)blockIdx.x * R * R;
-    for (int e = threadIdx.x; e < TS * TS; e += kBlock) {
-        const int r = rt * TS + e / TS, c = ct * TS + e % TS;
-        if (r < R && c < R) pb[r * R + c] = tile[e];
-    }
-}
 
 // Gram on the matrix cores: v_mfma_f64_16x16x4f64 multiplies a 16x4 by a
 // 4x16 FP64 tile.  For F^T F, a step covers 4 rows: lane l supplies
@@ -304,6 +224,68 @@ __global__ __launch_bounds__(BS) void k_gram_mfma_group(const GramJob *__restric
     gram_mfma_body<T, NT, BS, VEC>((const T *)j.F, j.rows, j.R, j.part, v.y, j.nblk);
 }
 
+// Ranks above 64 (up to 16 column tiles, 136 tile pairs): a block takes
+// kWidePairs of the pairs (blockIdx.y), nine per wave, whose sums fill a
+// wave's registers; its rows go through LDS 16 at a time, read by all four
+// waves; bound by FP64 MFMA.  R = 100, Grams of 120,000, 61,000 and 23,000
+// rows on average: BF16 393 -> 138 us (beside the MTTKRP), FP32 330 -> 82 us,
+// against 8 x 8 register tiles on the vector units.
+constexpr int kWideWavePairs = 9, kWidePairs = 4 * kWideWavePairs;
+
+template <typename T, int NTMAX>
+__global__ __launch_bounds__(kBlock) void k_gram_wide(const T *__restrict__ F, int64_t rows, int R,
+                                                      double *__restrict__ part) {
+    constexpr int RP = 16 * NTMAX;
+    __shared__ float sx[16][RP];
+    const int nt = (R + 15) / 16, npair = nt * (nt + 1) / 2;
+    const int lane = threadIdx.x % 64, wave = threadIdx.x / 64, kr = lane / 16, cl = lane % 16;
+    // this wave's pairs (rt <= ct), in row-major order of the upper triangle
+    int rt[kWideWavePairs], ct[kWideWavePairs];
+    const int q0 = blockIdx.y * kWidePairs + wave * kWideWavePairs;
+#pragma unroll
+    for (int i = 0; i < kWideWavePairs; ++i) {
+        int q = q0 + i < npair ? q0 + i : npair - 1, r = 0;
+        while (q >= nt - r) q -= nt - r, ++r;
+        rt[i] = r;
+        ct[i] = r + q;
+    }
+    double4v acc[kWideWavePairs];
+#pragma unroll
+    for (int i = 0; i < kWideWavePairs; ++i) acc[i] = double4v{0.0, 0.0, 0.0, 0.0};
+    for (int e = threadIdx.x; e < 16 * RP; e += kBlock) (&sx[0][0])[e] = 0.f;
+    const int64_t nstep = (rows + 15) / 16;
+    for (int64_t s = blockIdx.x; s < nstep; s += gridDim.x) {
+        const int64_t r0 = s * 16;
+        const int nr = (int)(rows - r0 < 16 ? rows - r0 : 16);
+        __syncthreads();
+        for (int e = threadIdx.x; e < 16 * R; e += kBlock) {
+            const int r = e / R;
+            sx[r][e - r * R] = r < nr ? ldf<T>(F, r0 * R + e) : 0.f;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 16; k += 4)
+#pragma unroll
+            for (int i = 0; i < kWideWavePairs; ++i)
+                acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(
+                    (double)sx[k + kr][16 * rt[i] + cl], (double)sx[k + kr][16 * ct[i] + cl],
+                    acc[i], 0, 0, 0);
+    }
+    double *pb = part + (size_t)blockIdx.x * R * R;
+#pragma unroll
+    for (int i = 0; i < kWideWavePairs; ++i) {
+        if (q0 + i >= npair) continue;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int r = 16 * rt[i] + kr + 4 * v, c = 16 * ct[i] + cl;
+            if (r < R && c < R) {
+                pb[r * R + c] = acc[i][v];
+                if (rt[i] != ct[i]) pb[c * R + r] = acc[i][v];
+            }
+        }
+    }
+}
+
 // G[e] = sum_b part[b][e]: a block takes 16 entries; slice q (16 per entry)
 // sums the partials b = q, q + 16, ...; the slices are combined in order.
 // The first 16 partials of a slice are loaded together, then added in order.
@@ -357,9 +339,10 @@ __global__ void k_hadamard(int R, const double *__restrict__ Gp, const double *_
     H[e] = Gp[e] * Gq[e] + ((e / R == e % R) ? reg : 0.0);
 }
 
-// fixed-order block reduction of one double per thread
+// fixed-order block reduction of one double per thread, over the first
+// kBlock threads (any others only join the barriers)
 __device__ double block_sum(double v, double *sh) {
-    sh[threadIdx.x] = v;
+    if (threadIdx.x < kBlock) sh[threadIdx.x] = v;
     __syncthreads();
     for (int w = kBlock / 2; w > 0; w >>= 1) {
         if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
@@ -371,7 +354,7 @@ __device__ double block_sum(double v, double *sh) {
 }
 
 __device__ double block_max(double v, double *sh) {
-    sh[threadIdx.x] = v;
+    if (threadIdx.x < kBlock) sh[threadIdx.x] = v;
     __syncthreads();
     for (int w = kBlock / 2; w > 0; w >>= 1) {
         if ((int)threadIdx.x < w) sh[threadIdx.x] = fmax(sh[threadIdx.x], sh[threadIdx.x + w]);
@@ -382,14 +365,13 @@ __device__ double block_max(double v, double *sh) {
     return r;
 }
 
-// R x R working matrices live in LDS up to these ranks (at most ~56 KB of
-// dynamic LDS), else in global scratch.
-constexpr int kSolveSmemMaxR = 44;   // 3 R^2 doubles
-constexpr int kLambdaSmemMaxR = 40;  // 4 R^2 + R doubles
+// The lambda step's R x R matrices live in LDS up to this rank (4 R^2 + R
+// doubles, at most 52 KB of dynamic LDS), else in global scratch.
+constexpr int kLambdaSmemMaxR = 40;
 
 // ---------------------------------------------------------------------------
 // one-workgroup solve.  Working set: 3 R^2 doubles (H, A, B / V), in
-// dynamic LDS when SMEM, else in `scratch`.  flag[0] = 1 when the
+// dynamic LDS when SMEM (R <= 32), else in `scratch`.  flag[0] = 1 when the
 // pseudo-inverse path was taken.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ double readlane_f64(double v, int lane) {
@@ -448,7 +430,82 @@ __device__ bool gauss_jordan_wave(const double *H, int R, double tol, double *Bw
     return true;
 }
 
-template <bool SMEM>
+// The same Gauss-Jordan for 32 < R <= 32 NT by a block of 1024 threads, the
+// matrix in their registers (thread (y, x) of 32 x 32 holds the entries (y +
+// 32 a, x + 32 b)) and in place: a column of [H | I] that a step has made a
+// unit column is never read again, so the column of the inverse takes its
+// place.  Operation for operation the arithmetic of the other two versions.
+// A step publishes its row, its column and 1 / pivot in LDS (two sets, so one
+// barrier per step), then every entry takes one FMA: R steps of about 0.3 us,
+// where sweeping [H | I] in global memory took 28 us each (R = 100: 2782 -> 101
+// us beside the MTTKRP).
+template <int NT>
+__device__ bool gauss_jordan_block(const double *__restrict__ Gp, const double *__restrict__ Gq,
+                                   double reg, int R, double tol, double *__restrict__ Bw) {
+    __shared__ double s_row[2][32 * NT], s_col[2][32 * NT], s_piv[2], s_inv[2];
+    const int x = threadIdx.x % 32, y = threadIdx.x / 32;
+    double a[NT][NT];
+#pragma unroll
+    for (int p = 0; p < NT; ++p)
+#pragma unroll
+        for (int q = 0; q < NT; ++q) {
+            const int i = y + 32 * p, k = x + 32 * q;
+            a[p][q] = i < R && k < R ? Gp[i * R + k] * Gq[i * R + k] + (i == k ? reg : 0.0) : 0.0;
+        }
+    bool ok = true;
+    // steps 32 t .. 32 t + 31 have their row in a[t][.] and their column in
+    // a[.][t], compile-time places
+    unroll_for<0, NT>([&](auto tc) {
+        constexpr int t = decltype(tc)::value;
+        for (int u = 0; u < 32; ++u) {
+            const int j = 32 * t + u, w = u & 1;
+            if (!ok || j >= R) break;  // uniform
+            if (y == u) {
+#pragma unroll
+                for (int q = 0; q < NT; ++q) s_row[w][x + 32 * q] = a[t][q];
+            }
+            if (x == u) {
+#pragma unroll
+                for (int p = 0; p < NT; ++p) s_col[w][y + 32 * p] = a[p][t];
+                if (y == u) {
+                    s_piv[w] = a[t][t];
+                    s_inv[w] = 1.0 / a[t][t];
+                }
+            }
+            __syncthreads();
+            ok = s_piv[w] > tol;
+            const double inv = s_inv[w];
+            double r[NT], c[NT];
+#pragma unroll
+            for (int q = 0; q < NT; ++q) r[q] = s_row[w][x + 32 * q] * inv;
+#pragma unroll
+            for (int p = 0; p < NT; ++p) c[p] = s_col[w][y + 32 * p];
+            if (x == u) r[t] = inv;  // the new column: e_j / pivot
+#pragma unroll
+            for (int p = 0; p < NT; ++p)
+#pragma unroll
+                for (int q = 0; q < NT; ++q) {
+                    const double old = q == t && x == u ? 0.0 : a[p][q];
+                    a[p][q] = p == t && y == u ? r[q] : fma(-c[p], r[q], old);
+                }
+        }
+    });
+    if (!ok) return false;
+#pragma unroll
+    for (int p = 0; p < NT; ++p)
+#pragma unroll
+        for (int q = 0; q < NT; ++q) {
+            const int i = y + 32 * p, k = x + 32 * q;
+            if (i < R && k < R) Bw[i * R + k] = a[p][q];
+        }
+    return true;
+}
+
+// BS threads (kBlock, or kSolveWide for launches with ranks above 32)
+constexpr int kSolveWide = 1024;
+constexpr int kSolveRegMaxR = 128;  // ranks that gauss_jordan_block takes
+
+template <int BS, bool SMEM>
 __device__ void solve_body(int R, const double *__restrict__ Gp, const double *__restrict__ Gq,
                            double reg, double *__restrict__ Hinv, double *__restrict__ scratch,
                            int *flag, double *dyn) {
@@ -460,14 +517,15 @@ __device__ void solve_body(int R, const double *__restrict__ Gp, const double *_
     const int RR = R * R;
     double *base = SMEM ? dyn : scratch;
     double *H = base, *L = base + RR, *Li = base + 2 * RR;
-    for (int e = tid; e < RR; e += kBlock) {
+    for (int e = tid; e < RR; e += BS) {
         H[e] = Gp[e] * Gq[e] + ((e / R == e % R) ? reg : 0.0);
         L[e] = 0.0;
         Li[e] = 0.0;
     }
     __syncthreads();
     double dm = 0.0;
-    for (int r = tid; r < R; r += kBlock) dm = fmax(dm, H[r * R + r]);
+    if (tid < kBlock)
+        for (int r = tid; r < R; r += kBlock) dm = fmax(dm, H[r * R + r]);
     const double dmax = block_max(dm, sh);
     const double tol = (double)R * DBL_EPSILON * dmax;
     if (tid == 0) s_fail = (dmax > 0.0) ? 0 : 1;
@@ -486,8 +544,15 @@ __device__ void solve_body(int R, const double *__restrict__ Gp, const double *_
             if (tid == 0 && !ok) s_fail = 1;
         }
         __syncthreads();
+    } else if (BS == kSolveWide && R <= kSolveRegMaxR) {
+        if (!s_fail) {
+            const bool ok = R <= 64   ? gauss_jordan_block<2>(Gp, Gq, reg, R, tol, Bw)
+                            : R <= 96 ? gauss_jordan_block<3>(Gp, Gq, reg, R, tol, Bw)
+                                      : gauss_jordan_block<4>(Gp, Gq, reg, R, tol, Bw);
+            if (tid == 0 && !ok) s_fail = 1;
+        }
     } else {
-        for (int e = tid; e < RR; e += kBlock) {
+        for (int e = tid; e < RR; e += BS) {
             Aw[e] = H[e];
             Bw[e] = (e / R == e % R) ? 1.0 : 0.0;
         }
@@ -500,13 +565,13 @@ __device__ void solve_body(int R, const double *__restrict__ Gp, const double *_
             }
             const double inv = 1.0 / piv;
             __syncthreads();  // all threads have read the pivot
-            for (int k = tid; k < 2 * R; k += kBlock) {
+            for (int k = tid; k < 2 * R; k += BS) {
                 if (k < R) Aw[j * R + k] *= inv;
                 else Bw[j * R + k - R] *= inv;
             }
-            for (int i = tid; i < R; i += kBlock) s_f[i] = (i == j) ? 0.0 : Aw[i * R + j];
+            for (int i = tid; i < R; i += BS) s_f[i] = (i == j) ? 0.0 : Aw[i * R + j];
             __syncthreads();
-            for (int e = tid; e < R * 2 * R; e += kBlock) {
+            for (int e = tid; e < R * 2 * R; e += BS) {
                 const int i = e / (2 * R), k = e % (2 * R);
                 const double f = s_f[i];
                 if (f == 0.0) continue;
@@ -518,7 +583,7 @@ __device__ void solve_body(int R, const double *__restrict__ Gp, const double *_
     }
     __syncthreads();
     if (!s_fail) {
-        for (int e = tid; e < RR; e += kBlock) {
+        for (int e = tid; e < RR; e += BS) {
             const int r = e / R, c = e % R;
             Hinv[e] = 0.5 * (Bw[r * R + c] + Bw[c * R + r]);
         }
@@ -527,7 +592,7 @@ __device__ void solve_body(int R, const double *__restrict__ Gp, const double *_
     }
     // pseudo-inverse: parallel cyclic Jacobi on A = H, V = I
     double *A = L, *V = Li;
-    for (int e = tid; e < RR; e += kBlock) {
+    for (int e = tid; e < RR; e += BS) {
         A[e] = H[e];
         V[e] = (e / R == e % R) ? 1.0 : 0.0;
     }
@@ -536,7 +601,8 @@ __device__ void solve_body(int R, const double *__restrict__ Gp, const double *_
     const int npair = n2 / 2;
     for (int sweep = 0; sweep < 100; ++sweep) {
         double off = 0.0, tot = 0.0;
-        for (int e = tid; e < RR; e += kBlock) {
+        // the first kBlock threads sum, so that the order does not depend on BS
+        for (int e = tid; tid < kBlock && e < RR; e += kBlock) {
             const double a2 = A[e] * A[e];
             tot += a2;
             if (e / R != e % R) off += a2;
@@ -545,7 +611,7 @@ __device__ void solve_body(int R, const double *__restrict__ Gp, const double *_
         tot = block_sum(tot, sh);
         if (off <= 1e-30 * tot || off == 0.0) break;
         for (int round = 0; round < n2 - 1; ++round) {
-            for (int pi = tid; pi < npair; pi += kBlock) {
+            for (int pi = tid; pi < npair; pi += BS) {
                 auto player = [&](int pos) { return pos == 0 ? 0 : 1 + (pos - 1 + round) % (n2 - 1); };
                 int p = player(pi), q = player(n2 - 1 - pi);
                 if (p > q) { const int t = p; p = q; q = t; }
@@ -567,7 +633,7 @@ __device__ void solve_body(int R, const double *__restrict__ Gp, const double *_
             }
             __syncthreads();
             // A <- A J and V <- V J (columns p, q of every disjoint pair)
-            for (int e = tid; e < npair * R; e += kBlock) {
+            for (int e = tid; e < npair * R; e += BS) {
                 const int pi = e / R, k = e % R;
                 const int p = s_p[pi], q = s_q[pi];
                 if (q >= R || s_s[pi] == 0.0) continue;
@@ -581,7 +647,7 @@ __device__ void solve_body(int R, const double *__restrict__ Gp, const double *_
             }
             __syncthreads();
             // A <- J^T A (rows p, q)
-            for (int e = tid; e < npair * R; e += kBlock) {
+            for (int e = tid; e < npair * R; e += BS) {
                 const int pi = e / R, k = e % R;
                 const int p = s_p[pi], q = s_q[pi];
                 if (q >= R || s_s[pi] == 0.0) continue;
@@ -594,10 +660,11 @@ __device__ void solve_body(int R, const double *__restrict__ Gp, const double *_
         }
     }
     double wm = 0.0;
-    for (int r = tid; r < R; r += kBlock) wm = fmax(wm, A[r * R + r]);
+    if (tid < kBlock)
+        for (int r = tid; r < R; r += kBlock) wm = fmax(wm, A[r * R + r]);
     const double wmax = block_max(wm, sh);
     const double wtol = (double)R * DBL_EPSILON * wmax;
-    for (int e = tid; e < RR; e += kBlock) {
+    for (int e = tid; e < RR; e += BS) {
         const int r = e / R, s = e % R;
         double acc = 0.0;
         for (int k = 0; k < R; ++k) {
@@ -609,20 +676,20 @@ __device__ void solve_body(int R, const double *__restrict__ Gp, const double *_
     if (tid == 0) flag[0] = 1;
 }
 
-template <bool SMEM>
-__global__ __launch_bounds__(kBlock) void k_solve(int R, const double *__restrict__ Gp,
-                                                  const double *__restrict__ Gq, double reg,
-                                                  double *__restrict__ Hinv,
-                                                  double *__restrict__ scratch, int *flag) {
+template <int BS, bool SMEM>
+__global__ __launch_bounds__(BS) void k_solve(int R, const double *__restrict__ Gp,
+                                              const double *__restrict__ Gq, double reg,
+                                              double *__restrict__ Hinv,
+                                              double *__restrict__ scratch, int *flag) {
     extern __shared__ double dyn[];
-    solve_body<SMEM>(R, Gp, Gq, reg, Hinv, scratch, flag, dyn);
+    solve_body<BS, SMEM>(R, Gp, Gq, reg, Hinv, scratch, flag, dyn);
 }
 
-template <bool SMEM>
-__global__ __launch_bounds__(kBlock) void k_solve_group(const SolveJob *__restrict__ jobs) {
+template <int BS, bool SMEM>
+__global__ __launch_bounds__(BS) void k_solve_group(const SolveJob *__restrict__ jobs) {
     extern __shared__ double dyn[];
     const SolveJob &j = jobs[blockIdx.x];
-    solve_body<SMEM>(j.R, j.Gp, j.Gq, j.reg, j.Hinv, j.scratch, j.flag, dyn);
+    solve_body<BS, SMEM>(j.R, j.Gp, j.Gq, j.reg, j.Hinv, j.scratch, j.flag, dyn);
 }
 
 // ---------------------------------------------------------------------------
@@ -677,6 +744,72 @@ __device__ void als_lambda_body(int R, int mode, const double *__restrict__ Hinv
         W[e] = ls > 0.0 ? Hi[e] / ls : 0.0;
         if (mode == 2) {
             in += Hi[e] * MM[e];
+            xh += lr * ls * GA[e] * GB[e] * g;
+        }
+    }
+    if (mode != 2) return;
+    in = block_sum(in, sh);
+    xh = block_sum(xh, sh);
+    if (tid == 0) {
+        double res2 = normsq + xh - 2.0 * in;
+        if (res2 < 0.0) res2 = 0.0;
+        *fit_out = normsq > 0.0 ? 1.0 - sqrt(res2) / sqrt(normsq) : 0.0;
+    }
+}
+
+// The lambda step of ranks above kLambdaSmemMaxR, spread over the device: one
+// block formed both R x R x R products from global memory (R = 100: 1103 us);
+// here each of the two takes a block per 16 x 16 tile, its operands staged in
+// LDS, and the rest one block (two products of 9 us and 27 us).  Every entry's sum runs over k in order, so the
+// results are bitwise those of als_lambda_body.
+constexpr int kMulTile = 16, kMulK = 64;
+// C = A B (R x R, row-major)
+__global__ __launch_bounds__(kBlock) void k_matmul(int R, const double *__restrict__ A,
+                                                   const double *__restrict__ B,
+                                                   double *__restrict__ C) {
+    __shared__ double sa[kMulTile][kMulK + 1], sb[kMulK][kMulTile + 1];
+    const int x = threadIdx.x % kMulTile, y = threadIdx.x / kMulTile;
+    const int r0 = blockIdx.y * kMulTile, c0 = blockIdx.x * kMulTile;
+    double acc = 0.0;
+    for (int k0 = 0; k0 < R; k0 += kMulK) {
+        __syncthreads();
+        for (int e = threadIdx.x; e < kMulTile * kMulK; e += kBlock) {
+            const int i = e / kMulK, k = e % kMulK;
+            sa[i][k] = r0 + i < R && k0 + k < R ? A[(r0 + i) * R + k0 + k] : 0.0;
+            const int kb = e / kMulTile, j = e % kMulTile;
+            sb[kb][j] = k0 + kb < R && c0 + j < R ? B[(k0 + kb) * R + c0 + j] : 0.0;
+        }
+        __syncthreads();
+        const int kn = R - k0 < kMulK ? R - k0 : kMulK;
+#pragma unroll 8
+        for (int k = 0; k < kn; ++k) acc = fma(sa[y][k], sb[k][x], acc);
+    }
+    if (r0 + y < R && c0 + x < R) C[(r0 + y) * R + c0 + x] = acc;
+}
+
+// lambda, G, W and (mode 2) the fit from S = H^-1 (M^T M) H^-1
+__global__ __launch_bounds__(kBlock) void k_lambda_finish(
+    int R, int mode, const double *__restrict__ Hi, const double *__restrict__ MM,
+    const double *__restrict__ S, double *__restrict__ Gn, double *__restrict__ W,
+    double *__restrict__ lambda_out, const double *__restrict__ GA,
+    const double *__restrict__ GB, double normsq, double *__restrict__ fit_out) {
+    __shared__ double sh[kBlock], lam[DFACTO_MAX_R];
+    const int tid = threadIdx.x, RR = R * R;
+    for (int r = tid; r < R; r += kBlock) {
+        const double d = S[r * R + r];
+        lam[r] = d > 0.0 ? sqrt(d) : 0.0;
+        lambda_out[r] = lam[r];
+    }
+    __syncthreads();
+    double in = 0.0, xh = 0.0;
+#pragma unroll 4
+    for (int e = tid; e < RR; e += kBlock) {
+        const double lr = lam[e / R], ls = lam[e % R], hi = Hi[e];
+        const double g = (lr > 0.0 && ls > 0.0) ? S[e] / (lr * ls) : 0.0;
+        Gn[e] = g;
+        W[e] = ls > 0.0 ? hi / ls : 0.0;
+        if (mode == 2) {
+            in += hi * MM[e];
             xh += lr * ls * GA[e] * GB[e] * g;
         }
     }
@@ -776,15 +909,14 @@ __global__ __launch_bounds__(kBlock) void k_fit_finish_group(const FitJob *__res
     fit_finish_body(j.R, j.lambda, j.GA, j.GB, j.GC, j.part, j.nblk, j.normsq, j.fit, sh);
 }
 
-template <bool SMEM>
 __global__ __launch_bounds__(kBlock) void k_als_lambda(
     int R, int mode, const double *__restrict__ Hinv_g, const double *__restrict__ MtM_g,
     double *__restrict__ Gn, double *__restrict__ W, double *__restrict__ lambda_out,
     const double *__restrict__ GA, const double *__restrict__ GB, double normsq,
-    double *__restrict__ fit_out, double *__restrict__ scratch) {
+    double *__restrict__ fit_out) {
     extern __shared__ double dyn[];
-    als_lambda_body<SMEM>(R, mode, Hinv_g, MtM_g, Gn, W, lambda_out, GA, GB, normsq, fit_out,
-                          scratch, dyn);
+    als_lambda_body<true>(R, mode, Hinv_g, MtM_g, Gn, W, lambda_out, GA, GB, normsq, fit_out,
+                          nullptr, dyn);
 }
 
 template <bool SMEM>
@@ -807,15 +939,6 @@ constexpr int kTileElems = 4096;
 constexpr int kCT = 16;  // columns per thread
 
 __host__ __device__ constexpr int tile_rows(int R) { return kTileElems / R < kBlock ? kTileElems / R : kBlock; }
-
-template <typename T>
-__device__ __forceinline__ float ldf(const T *p, int64_t i);
-template <>
-__device__ __forceinline__ float ldf<float>(const float *p, int64_t i) { return p[i]; }
-template <>
-__device__ __forceinline__ float ldf<uint16_t>(const uint16_t *p, int64_t i) {
-    return __uint_as_float((uint32_t)p[i] << 16);
-}
 
 // F[row, s] = sum_k M[row, k] W[k, s]   (R is a compile-time constant)
 template <typename Tout, int R>
@@ -1496,11 +1619,6 @@ __global__ __launch_bounds__(kBlock) void k_joint_f(const double *__restrict__ f
     if (threadIdx.x == 0) *f = mu * ft[0] + 0.5 * lam * tr + 0.5 * (normsq_y - in);
 }
 
-// 16-byte row loads are allowed when every row start is 16-byte aligned
-int vec_rows(const void *p, int R, int elem) {
-    return ((uintptr_t)p % 16 == 0) && (((size_t)R * elem) % 16 == 0);
-}
-
 // ---------------------------------------------------------------------------
 // Row maps on the matrix cores, R = 16 * NCT (16, 32, 48, 64).
 //
@@ -1675,6 +1793,162 @@ __global__ __launch_bounds__(kBlock) void k_gd_rows_mfma(float *__restrict__ G,
     if (threadIdx.x == 0) partial[blockIdx.x] = tot;
 }
 
+// Row maps of any rank up to 128 (and of any alignment).  A block takes 16 RS
+// rows at a time through LDS, coalesced both ways.  Its four waves are RS row
+// tiles times 4 / RS pairs of output column tiles; a wave keeps its pair's
+// R x 32 part of the matrix in registers as the A operand, the rows are the B
+// operand.  The per-element loops read both factors of every FMA from LDS:
+// R = 100, the same three factors 381 -> 124 us on average; gradient rows at
+// R = 10, 350,000 rows 190 -> 73 us (beside the MTTKRP).
+template <int NCT>
+struct RowAny {
+    static constexpr int RS = NCT <= 2 ? 4 : (NCT <= 4 ? 2 : 1);  // row tiles per block
+    static constexpr int TR = 16 * RS;                           // rows per block and step
+    static constexpr int RP = 16 * NCT + 1;                      // LDS row
+    static constexpr int S = 4 * NCT;                            // contraction steps
+};
+
+// wa[c][t] = W[4 t + lane / 16][16 (2 cg + c) + lane % 16], zero beyond R
+template <int NCT>
+__device__ __forceinline__ void load_any(const double *__restrict__ W, int R, int cg,
+                                         double (&wa)[2][RowAny<NCT>::S]) {
+    const int lane = threadIdx.x % 64;
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int t = 0; t < RowAny<NCT>::S; ++t) {
+            const int k = 4 * t + lane / 16, col = 16 * (2 * cg + c) + lane % 16;
+            wa[c][t] = k < R && col < R ? W[k * R + col] : 0.0;
+        }
+}
+
+// F[row, s] = sum_k M[row, k] W[k, s]
+template <typename Tout, int NCT>
+__global__ __launch_bounds__(kBlock) void k_rowmap_any(const float *__restrict__ M, int64_t rows,
+                                                       int R, const double *__restrict__ W,
+                                                       Tout *__restrict__ F) {
+    using A = RowAny<NCT>;
+    __shared__ float sx[A::TR * A::RP], so[A::TR * A::RP];
+    const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
+    const int rs = wave % A::RS, cg = wave / A::RS;
+    double wa[2][A::S];
+    load_any<NCT>(W, R, cg, wa);
+    for (int e = threadIdx.x; e < A::TR * A::RP; e += kBlock) sx[e] = 0.f;
+    const int64_t ntile = (rows + A::TR - 1) / A::TR;
+    for (int64_t tile = blockIdx.x; tile < ntile; tile += gridDim.x) {
+        const int64_t r0 = tile * A::TR;
+        const int n = (int)(rows - r0 < A::TR ? rows - r0 : A::TR) * R;
+        __syncthreads();
+        for (int e = threadIdx.x; e < n; e += kBlock) {
+            const int r = e / R;
+            sx[r * A::RP + e - r * R] = M[r0 * R + e];
+        }
+        __syncthreads();
+        const float *x = sx + (16 * rs + lane % 16) * A::RP + lane / 16;
+        double4v acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
+#pragma unroll
+        for (int t = 0; t < A::S; ++t)
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+                if (2 * cg + c < NCT)
+                    acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(wa[c][t], (double)x[4 * t],
+                                                                  acc[c], 0, 0, 0);
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+            if (2 * cg + c < NCT) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    so[(16 * rs + lane % 16) * A::RP + 16 * (2 * cg + c) + lane / 16 + 4 * v] =
+                        (float)acc[c][v];
+            }
+        __syncthreads();
+        for (int e = threadIdx.x; e < n; e += kBlock) {
+            const int r = e / R;
+            st_out<Tout>(F, r0 * R + e, (double)so[r * A::RP + e - r * R]);
+        }
+    }
+}
+
+// G[row, s] = -G[row, s] + sum_k F[row, k] H[k, s]  (G holds the MTTKRP);
+// partial[block] = sum over the block's rows of <F[row,:], M[row,:]>.
+template <typename T, int NCT>
+__global__ __launch_bounds__(kBlock) void k_gd_rows_any(float *__restrict__ G,
+                                                        const T *__restrict__ F, int64_t rows,
+                                                        int R, const double *__restrict__ H,
+                                                        double *__restrict__ partial) {
+    using A = RowAny<NCT>;
+    __shared__ float sx[A::TR * A::RP], so[A::TR * A::RP];
+    __shared__ double sh[kBlock];
+    const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
+    const int rs = wave % A::RS, cg = wave / A::RS;
+    double wa[2][A::S];
+    load_any<NCT>(H, R, cg, wa);
+    for (int e = threadIdx.x; e < A::TR * A::RP; e += kBlock) sx[e] = so[e] = 0.f;
+    double inner = 0.0;
+    const int64_t ntile = (rows + A::TR - 1) / A::TR;
+    for (int64_t tile = blockIdx.x; tile < ntile; tile += gridDim.x) {
+        const int64_t r0 = tile * A::TR;
+        const int n = (int)(rows - r0 < A::TR ? rows - r0 : A::TR) * R;
+        __syncthreads();
+        for (int e = threadIdx.x; e < n; e += kBlock) {
+            const int r = e / R, o = r * A::RP + e - r * R;
+            const float f = ldf<T>(F, r0 * R + e), m = G[r0 * R + e];
+            sx[o] = f;
+            so[o] = m;
+            inner = fma((double)f, (double)m, inner);
+        }
+        __syncthreads();
+        const float *x = sx + (16 * rs + lane % 16) * A::RP + lane / 16;
+        float *m = so + (16 * rs + lane % 16) * A::RP + 32 * cg + lane / 16;
+        double4v acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
+#pragma unroll
+        for (int t = 0; t < A::S; ++t)
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+                if (2 * cg + c < NCT)
+                    acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(wa[c][t], (double)x[4 * t],
+                                                                  acc[c], 0, 0, 0);
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+            if (2 * cg + c < NCT) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    float *o = m + 16 * c + 4 * v;
+                    *o = (float)(acc[c][v] - (double)*o);
+                }
+            }
+        __syncthreads();
+        for (int e = threadIdx.x; e < n; e += kBlock) {
+            const int r = e / R;
+            G[r0 * R + e] = so[r * A::RP + e - r * R];
+        }
+    }
+    const double tot = block_sum(inner, sh);
+    if (threadIdx.x == 0) partial[blockIdx.x] = tot;
+}
+
+constexpr int kRowAnyMaxR = 128;
+
+// f(integral_constant<int, NCT>) for the column tiles of rank R <= kRowAnyMaxR
+template <typename Fn>
+void with_tiles(int R, Fn &&f) {
+    switch ((R + 15) / 16) {
+        case 1: return f(std::integral_constant<int, 1>{});
+        case 2: return f(std::integral_constant<int, 2>{});
+        case 3: return f(std::integral_constant<int, 3>{});
+        case 4: return f(std::integral_constant<int, 4>{});
+        case 5: return f(std::integral_constant<int, 5>{});
+        case 6: return f(std::integral_constant<int, 6>{});
+        case 7: return f(std::integral_constant<int, 7>{});
+        default: return f(std::integral_constant<int, 8>{});
+    }
+}
+
+unsigned rows_grid_any(int64_t rows, int R) {
+    const int nct = (R + 15) / 16, tr = 16 * (nct <= 2 ? 4 : (nct <= 4 ? 2 : 1));
+    return (unsigned)std::max<int64_t>(1, std::min<int64_t>((rows + tr - 1) / tr, 2048));
+}
+
 // ranks with a matrix-core row kernel; the rows must start 16-byte aligned
 // (FP32) or 8-byte aligned (BF16)
 bool mfma_rows_ok(int R, const void *a, size_t ea, const void *b, size_t eb) {
@@ -1721,14 +1995,6 @@ bool tiled_rows_ok(int R) {  // ranks with a compile-time LDS-tiled row kernel (
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-
-int gram_partial_blocks(int64_t rows, int R) {
-    const int TS = R <= 16 ? 16 : (R <= 32 ? 32 : 64);
-    const int TT = TS / 8;
-    const int SL = kBlock / (TT * TT);
-    const int64_t want = (rows + (int64_t)SL * 16 - 1) / ((int64_t)SL * 16);
-    return (int)std::max<int64_t>(1, std::min<int64_t>(want, 256));
-}
 
 GramPlan gram_plan(int64_t rows, int R, const void *F, dfacto_dtype dtype) {
     GramPlan g;
@@ -1783,24 +2049,23 @@ void launch_gram(dfacto_ctx *ctx, const void *F, dfacto_dtype dtype, int64_t row
         DF_LAUNCHED();
         return;
     }
-    const int TS = R <= 16 ? 16 : (R <= 32 ? 32 : 64);
-    const int nt = (R + TS - 1) / TS;
-    const int nblk = gram_partial_blocks(rows, R);
+    const int nt = (R + 15) / 16, npair = nt * (nt + 1) / 2;
+    // at least four 16-row steps per block
+    const int nblk = (int)std::max<int64_t>(1, std::min<int64_t>((rows + 63) / 64, 256));
     // sized for the largest block count so that the buffer never moves between calls
     double *part = (double *)ws_get(ctx, gram_slot(ctx), sizeof(double) * 256 * (size_t)R * R);
-    dim3 grid(nblk, nt * nt);
-    const int vec = vec_rows(F, R, dtype == DFACTO_F32 ? 4 : 2);
-#define GRAM_LAUNCH(T, TSV)                                                                   \
-    hipLaunchKernelGGL((k_gram_partial<T, TSV>), grid, dim3(kBlock), 0, s, (const T *)F, rows, R, \
-                       vec, part)
+    const dim3 grid(nblk, (npair + kWidePairs - 1) / kWidePairs);
+#define GRAM_LAUNCH(T)                                                                          \
+    if (nt <= 8)                                                                                \
+        hipLaunchKernelGGL((k_gram_wide<T, 8>), grid, dim3(kBlock), 0, s, (const T *)F, rows, R, \
+                           part);                                                               \
+    else                                                                                        \
+        hipLaunchKernelGGL((k_gram_wide<T, 16>), grid, dim3(kBlock), 0, s, (const T *)F, rows, R, \
+                           part)
     if (dtype == DFACTO_F32) {
-        if (TS == 16) GRAM_LAUNCH(float, 16);
-        else if (TS == 32) GRAM_LAUNCH(float, 32);
-        else GRAM_LAUNCH(float, 64);
+        GRAM_LAUNCH(float);
     } else {
-        if (TS == 16) GRAM_LAUNCH(uint16_t, 16);
-        else if (TS == 32) GRAM_LAUNCH(uint16_t, 32);
-        else GRAM_LAUNCH(uint16_t, 64);
+        GRAM_LAUNCH(uint16_t);
     }
 #undef GRAM_LAUNCH
     hipLaunchKernelGGL(k_gram_reduce, dim3((R * R + 15) / 16), dim3(kBlock), 0, s, part, nblk, R, G);
@@ -1816,12 +2081,13 @@ void launch_hadamard(dfacto_ctx *ctx, int R, const double *Gp, const double *Gq,
 
 void launch_solve(dfacto_ctx *ctx, int R, const double *Gp, const double *Gq, double reg,
                   double *Hinv, double *scratch, int *flag) {
-    if (R <= kSolveSmemMaxR)
-        hipLaunchKernelGGL(k_solve<true>, dim3(1), dim3(kBlock), sizeof(double) * 3 * R * R,
-                           ctx->stream, R, Gp, Gq, reg, Hinv, scratch, flag);
+    if (R <= 32)
+        hipLaunchKernelGGL((k_solve<kBlock, true>), dim3(1), dim3(kBlock),
+                           sizeof(double) * 3 * R * R, ctx->stream, R, Gp, Gq, reg, Hinv, scratch,
+                           flag);
     else
-        hipLaunchKernelGGL(k_solve<false>, dim3(1), dim3(kBlock), 0, ctx->stream, R, Gp, Gq, reg,
-                           Hinv, scratch, flag);
+        hipLaunchKernelGGL((k_solve<kSolveWide, false>), dim3(1), dim3(kSolveWide), 0, ctx->stream,
+                           R, Gp, Gq, reg, Hinv, scratch, flag);
     DF_LAUNCHED();
 }
 
@@ -1829,12 +2095,17 @@ void launch_als_lambda(dfacto_ctx *ctx, int R, int mode, const double *Hinv, con
                        double *Gn, double *W, double *lambda_out, const double *GA,
                        const double *GB, double normsq, double *fit_out, double *scratch) {
     if (R <= kLambdaSmemMaxR)
-        hipLaunchKernelGGL(k_als_lambda<true>, dim3(1), dim3(kBlock),
-                           sizeof(double) * (4 * R * R + R), ctx->stream, R, mode, Hinv, MtM, Gn, W,
-                           lambda_out, GA, GB, normsq, fit_out, scratch);
-    else
-        hipLaunchKernelGGL(k_als_lambda<false>, dim3(1), dim3(kBlock), 0, ctx->stream, R, mode,
-                           Hinv, MtM, Gn, W, lambda_out, GA, GB, normsq, fit_out, scratch);
+        hipLaunchKernelGGL(k_als_lambda, dim3(1), dim3(kBlock), sizeof(double) * (4 * R * R + R),
+                           ctx->stream, R, mode, Hinv, MtM, Gn, W, lambda_out, GA, GB, normsq,
+                           fit_out);
+    else {
+        double *T1 = scratch, *S = scratch + (size_t)R * R;
+        const unsigned nt = (unsigned)(R + kMulTile - 1) / kMulTile;
+        hipLaunchKernelGGL(k_matmul, dim3(nt, nt), dim3(kBlock), 0, ctx->stream, R, MtM, Hinv, T1);
+        hipLaunchKernelGGL(k_matmul, dim3(nt, nt), dim3(kBlock), 0, ctx->stream, R, Hinv, T1, S);
+        hipLaunchKernelGGL(k_lambda_finish, dim3(1), dim3(kBlock), 0, ctx->stream, R, mode, Hinv,
+                           MtM, S, Gn, W, lambda_out, GA, GB, normsq, fit_out);
+    }
     DF_LAUNCHED();
 }
 
@@ -1903,7 +2174,18 @@ void launch_rowmap(dfacto_ctx *ctx, const float *M, int64_t rows, int R, const d
     const bool done = dtype == DFACTO_F32
                           ? dispatch_tiled<RowmapK, float>(R, s, M, rows, W, F)
                           : dispatch_tiled<RowmapK, uint16_t>(R, s, M, rows, W, F);
-    if (!done) {
+    if (!done && R <= kRowAnyMaxR) {
+        with_tiles(R, [&](auto nc) {
+            constexpr int NCT = decltype(nc)::value;
+            const dim3 g(rows_grid_any(rows, R)), b(kBlock);
+            if (dtype == DFACTO_F32)
+                hipLaunchKernelGGL((k_rowmap_any<float, NCT>), g, b, 0, s, M, rows, R, W,
+                                   (float *)F);
+            else
+                hipLaunchKernelGGL((k_rowmap_any<uint16_t, NCT>), g, b, 0, s, M, rows, R, W,
+                                   (uint16_t *)F);
+        });
+    } else if (!done) {
         const unsigned g = rows_grid_generic(rows, R, kBlock * 4);
         if (dtype == DFACTO_F32)
             hipLaunchKernelGGL(k_rowmap_g<float>, dim3(g), dim3(kBlock), 0, s, M, rows, R, W,
@@ -1917,8 +2199,9 @@ void launch_rowmap(dfacto_ctx *ctx, const float *M, int64_t rows, int R, const d
 
 int gd_rows_partials(int64_t rows, int R, const float *G, const void *F, dfacto_dtype dtype) {
     if (mfma_rows_ok(R, G, 4, F, dtype == DFACTO_F32 ? 4 : 2)) return (int)rows_grid_mfma(rows);
-    return (int)(tiled_rows_ok(R) ? rows_grid_tiles(rows, R)
-                                  : rows_grid_generic(rows, R, kBlock * 2));
+    return (int)(tiled_rows_ok(R)     ? rows_grid_tiles(rows, R)
+                 : R <= kRowAnyMaxR ? rows_grid_any(rows, R)
+                                      : rows_grid_generic(rows, R, kBlock * 2));
 }
 
 void launch_gd_rows(dfacto_ctx *ctx, float *G, const void *F, dfacto_dtype dtype, int64_t rows,
@@ -1934,7 +2217,18 @@ void launch_gd_rows(dfacto_ctx *ctx, float *G, const void *F, dfacto_dtype dtype
     const bool done = dtype == DFACTO_F32
                           ? dispatch_tiled<GdRowsK, float>(R, s, G, F, rows, H, inner_partial)
                           : dispatch_tiled<GdRowsK, uint16_t>(R, s, G, F, rows, H, inner_partial);
-    if (!done) {
+    if (!done && R <= kRowAnyMaxR) {
+        with_tiles(R, [&](auto nc) {
+            constexpr int NCT = decltype(nc)::value;
+            const dim3 g(rows_grid_any(rows, R)), b(kBlock);
+            if (dtype == DFACTO_F32)
+                hipLaunchKernelGGL((k_gd_rows_any<float, NCT>), g, b, 0, s, G, (const float *)F,
+                                   rows, R, H, inner_partial);
+            else
+                hipLaunchKernelGGL((k_gd_rows_any<uint16_t, NCT>), g, b, 0, s, G,
+                                   (const uint16_t *)F, rows, R, H, inner_partial);
+        });
+    } else if (!done) {
         const unsigned g = (unsigned)gd_rows_partials(rows, R, G, F, dtype);
         if (dtype == DFACTO_F32)
             hipLaunchKernelGGL(k_gd_rows_g<float>, dim3(g), dim3(kBlock), 0, s, G,
@@ -2127,11 +2421,12 @@ void launch_gram_reduce_group(dfacto_ctx *ctx, const GramJob *d_jobs, const uint
 
 void launch_solve_group(dfacto_ctx *ctx, int maxR, const SolveJob *d_jobs, uint32_t n) {
     if (n == 0) return;
-    if (maxR <= kSolveSmemMaxR)
-        hipLaunchKernelGGL(k_solve_group<true>, dim3(n), dim3(kBlock),
+    if (maxR <= 32)
+        hipLaunchKernelGGL((k_solve_group<kBlock, true>), dim3(n), dim3(kBlock),
                            sizeof(double) * 3 * maxR * maxR, ctx->stream, d_jobs);
     else
-        hipLaunchKernelGGL(k_solve_group<false>, dim3(n), dim3(kBlock), 0, ctx->stream, d_jobs);
+        hipLaunchKernelGGL((k_solve_group<kSolveWide, false>), dim3(n), dim3(kSolveWide), 0,
+                           ctx->stream, d_jobs);
     DF_LAUNCHED();
 }
 
