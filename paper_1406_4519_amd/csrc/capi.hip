@@ -153,6 +153,10 @@ Small small_ws(dfacto_ctx *ctx, int R) {
 
 namespace dfacto {
 
+// what a context's build pool may keep between builds (and until the context
+// is destroyed): the temporaries of about a million nonzeros
+constexpr uint64_t kBuildPoolKeep = (uint64_t)128 << 20;
+
 dfacto_status build_flattenings_impl(dfacto_ctx *ctx, const int64_t dims[3], int64_t nnz,
                                      const uint32_t *d_i, const uint32_t *d_j,
                                      const uint32_t *d_k, const float *d_val, dfacto_tensor **out,
@@ -188,8 +192,8 @@ dfacto_status build_flattenings_impl(dfacto_ctx *ctx, const int64_t dims[3], int
         // Without a memory source of the caller's, the build's temporaries
         // come from a pool of the context that keeps freed memory mapped
         // until the build ends (memory given back to the device is mapped
-        // afresh, and cleared, at each later allocation), then gives it all
-        // back.
+        // afresh, and cleared, at each later allocation), then gives back
+        // all but kBuildPoolKeep, which the next build finds mapped.
         hipMemPool_t pool = nullptr;
         if (!ctx->mem.has_user() && !ctx->mem.pool) {
             if (!ctx->build_pool) {
@@ -211,8 +215,13 @@ dfacto_status build_flattenings_impl(dfacto_ctx *ctx, const int64_t dims[3], int
         auto drop_pool = [&] {
             if (!pool) return;
             ctx->mem.pool = nullptr;
+            uint64_t held = UINT64_MAX;
+            if (hipMemPoolGetAttribute(pool, hipMemPoolAttrReservedMemCurrent, &held) !=
+                hipSuccess)
+                (void)hipGetLastError();
+            if (held <= kBuildPoolKeep) return;
             (void)hipStreamSynchronize(ctx->stream);  // the temporaries' frees
-            (void)hipMemPoolTrimTo(pool, 0);
+            (void)hipMemPoolTrimTo(pool, kBuildPoolKeep);
         };
         ctx->mem.pool = pool ? pool : ctx->mem.pool;
         try {

@@ -48,8 +48,6 @@ struct ModeData {
     int64_t nruns_short = 0;
     uint32_t *runs_long = nullptr;
     int64_t nruns_long = 0;
-    // host copies of the run lists (the sources of their uploads)
-    std::vector<uint32_t> runs_short_host, runs_long_host;
     // Relabeled gathers (null when the stream holds the original indices):
     // the stream's leaf and mid indices are ranks in the order of decreasing
     // gather count (nonzeros per leaf row, fiber headers per mid row; ties
@@ -266,7 +264,7 @@ struct dfacto_ctx {
     size_t ws_size[kNumSlots] = {};
     bool frozen = false;  // dfacto_ctx_freeze: workspaces may not grow
     // build temporaries without a caller's memory source (created on the
-    // first build; empty between builds)
+    // first build; holds at most kBuildPoolKeep between builds)
     hipMemPool_t build_pool = nullptr;
     // kernel timing (dfacto_profile_*)
     bool profiling = false;
