@@ -191,13 +191,17 @@ __global__ __launch_bounds__(kThreads) void k_tile_distinct(C c, int64_t n,
 // distinct one, entry e.  Runs of more than kRunShort entries are listed as
 // (o, e) and left to k_merge_long: adding up the 100,000 draws of a skewed
 // tensor's most frequent coordinate in one thread took 16 ms, a memory round
-// trip per entry.
-constexpr int kRunShort = 32;
+// trip per entry (50M draws now: 0.73 + 0.54 ms; one global atomic per listed
+// run instead of per tile: 2.25 + 0.6).
+constexpr int kRunShort = 16;
 template <class C, class Store>
 __global__ __launch_bounds__(kThreads) void k_merge(C c, const float *__restrict__ v, int64_t n,
                                                     const uint32_t *__restrict__ off, Store store,
                                                     uint2 *__restrict__ longs,
                                                     uint32_t *__restrict__ nlong) {
+    __shared__ uint2 sl[kTile / (kRunShort + 1) + 2];  // the long runs that begin here
+    __shared__ uint32_t nsl;
+    if (threadIdx.x == 0) nsl = 0;
     uint64_t mask[kTileSlots];
     uint32_t k = 0;
 #pragma unroll
@@ -212,21 +216,31 @@ __global__ __launch_bounds__(kThreads) void k_merge(C c, const float *__restrict
     const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int q = 0; q < kTileSlots; ++q) {
+        const int64_t e = tile_entry(q);
+        const uint32_t at = o + (uint32_t)__popcll(mask[q] & ~(~0ull << lane));
+        bool lng = false;
         if ((mask[q] >> lane) & 1) {
-            const int64_t e = tile_entry(q);
-            const uint32_t at = o + (uint32_t)__popcll(mask[q] & ~(~0ull << lane));
             float sum = v[e];
             int64_t t = e + 1;
-            for (; t < n && t <= e + kRunShort && c.same(t, e); ++t) sum += v[t];
-            if (t == e + kRunShort + 1) longs[atomicAdd(nlong, 1u)] = make_uint2(at, (uint32_t)e);
-            else store(at, e, sum);
+            if (lane == 63 || !((mask[q] >> (lane + 1)) & 1))
+                for (; t < n && t <= e + kRunShort && c.same(t, e); ++t) sum += v[t];
+            lng = t == e + kRunShort + 1;
+            if (!lng) store(at, e, sum);
         }
+        if (lng) sl[atomicAdd(&nsl, 1u)] = make_uint2(at, (uint32_t)e);
         o += (uint32_t)__popcll(mask[q]);
     }
+    // the tile's runs take consecutive places in the list: one global atomic
+    __syncthreads();
+    __shared__ uint32_t place;
+    if (threadIdx.x == 0 && nsl) place = atomicAdd(nlong, nsl);
+    __syncthreads();
+    for (uint32_t r = threadIdx.x; r < nsl; r += kThreads) longs[place + r] = sl[r];
 }
 
-// One wave per listed run: 1024 values at a time through LDS, added in order
-// while the next ones are loaded.  Bound by the chain of adds.
+// One wave per listed run: its end by a search with 64 probes at a time, then
+// 1024 values at a time through LDS, added in order while the next ones are in
+// flight.  Bound by the chain of adds.
 constexpr int kLongSlots = 16, kLongBatch = 64 * kLongSlots;
 template <class C, class Store>
 __global__ __launch_bounds__(64) void k_merge_long(C c, const float *__restrict__ v, int64_t n,
@@ -237,40 +251,48 @@ __global__ __launch_bounds__(64) void k_merge_long(C c, const float *__restrict_
     for (uint32_t r = blockIdx.x; r < *nlong; r += gridDim.x) {
         const uint2 w = longs[r];
         const int64_t e = w.y;
+        // the run is [e, end): lo is in it, hi is not
+        int64_t lo = e, hi = n, step = 1;
+        while (hi - lo > 1) {
+            const int64_t t = lo + (lane + 1) * step;
+            const uint64_t in = __ballot(t < hi && c.same(t, e));
+            const int k = __popcll(in);  // sorted: the first k probes
+            if (k < 64) hi = lo + (k + 1) * step < hi ? lo + (k + 1) * step : hi;
+            lo += k * step;
+            step = k == 64 ? step * 64 : (hi - lo + 62) / 64;
+            if (step < 1) step = 1;
+        }
+        const int64_t end = hi;
         float next[kLongSlots];
-        auto load = [&](int64_t at) {  // returns the run's entries among them
-            int len = 0;
+        auto load = [&](int64_t at) {
 #pragma unroll
             for (int q = 0; q < kLongSlots; ++q) {
                 const int64_t t = at + q * 64 + lane;
-                const bool in = t < n && c.same(t, e);
-                next[q] = in ? v[t] : 0.f;
-                len += (int)__popcll(__ballot(in));
+                next[q] = v[t < end ? t : end - 1];
             }
-            return len;
         };
-        int len = load(e);
+        load(e);
         float sum = 0.f;
-        for (int64_t at = e;; at += kLongBatch) {
-            const int have = len;
+        for (int64_t at = e; at < end; at += kLongBatch) {
+            const int have = (int)(end - at < kLongBatch ? end - at : kLongBatch);
             __syncthreads();
 #pragma unroll
             for (int q = 0; q < kLongSlots; ++q) x[q * 64 + lane] = next[q];
             __syncthreads();
-            if (have == kLongBatch) len = load(at + kLongBatch);
+            load(at + kLongBatch);
             int k = 0;
             if (at == e) sum = x[k++];  // the first value itself
-            for (; k < have && (k & 15); ++k) sum += x[k];
-            for (; k + 16 <= have; k += 16) {
-                const float4 a = *(const float4 *)(x + k), b = *(const float4 *)(x + k + 4),
-                             d = *(const float4 *)(x + k + 8), f = *(const float4 *)(x + k + 12);
-                sum += a.x; sum += a.y; sum += a.z; sum += a.w;
-                sum += b.x; sum += b.y; sum += b.z; sum += b.w;
-                sum += d.x; sum += d.y; sum += d.z; sum += d.w;
-                sum += f.x; sum += f.y; sum += f.z; sum += f.w;
+            for (; k < have && (k & 63); ++k) sum += x[k];
+            for (; k + 64 <= have; k += 64) {
+                float4 a[16];  // all reads ahead of the chain of adds
+#pragma unroll
+                for (int q = 0; q < 16; ++q) a[q] = *(const float4 *)(x + k + 4 * q);
+#pragma unroll
+                for (int q = 0; q < 16; ++q) {
+                    sum += a[q].x; sum += a[q].y; sum += a[q].z; sum += a[q].w;
+                }
             }
             for (; k < have; ++k) sum += x[k];
-            if (have < kLongBatch) break;
         }
         if (lane == 0) store(w.x, e, sum);
     }
@@ -394,7 +416,7 @@ __global__ void k_scan_apply(const uint32_t *__restrict__ in, uint32_t *__restri
 // Bound by HBM: a pass reads the keys for the histograms, then reads and
 // writes keys and values (32 bytes per pair).  A tile's pairs are put in digit
 // order in LDS first, so that each digit's run leaves as one piece of
-// consecutive stores.
+// consecutive stores: 50M pairs 478 + 120 us per pass -> 311 + 100 (3.9 TB/s).
 // ---------------------------------------------------------------------------
 constexpr int kRadixSlots = 16;  // pairs per thread
 constexpr int kRadixTile = kThreads * kRadixSlots;
@@ -448,7 +470,7 @@ __global__ __launch_bounds__(kThreads) void k_radix_scatter(
     if constexpr (kOwn) {  // offs holds the histograms here
         uint32_t tot = 0, pre = 0;
         if ((uint32_t)tid <= dmask) {
-#pragma unroll 8
+#pragma unroll 32
             for (int b = 0; b < (int)nblk; ++b) {
                 const uint32_t c = offs[b * 256 + tid];
                 tot += c;
@@ -743,17 +765,33 @@ __global__ void k_compact_rows(const uint32_t *__restrict__ mark, const uint32_t
     }
 }
 
-// chunk c starts at the first header at or after c * len (or at the end)
+// chunk c starts at the first header at or after c * len (or at the end): a
+// wave looks at 64 entries at a time (a header comes every kFiberCap + 1 at
+// least).  heads[c]: that entry (a chunk at the end counts as opening a row).
 __global__ void k_chunk_starts(const uint2 *__restrict__ st, int64_t nentry, int64_t nchunk,
-                               int len, uint32_t *__restrict__ cs) {
-    GRID_STRIDE(c, nchunk + 1) {
-        int64_t p = c * (int64_t)len;
-        if (c == nchunk || p >= nentry) {
-            p = nentry;
-        } else {
-            while (p < nentry && !(st[p].x & kHdrBit)) ++p;
+                               int len, uint32_t *__restrict__ cs, uint2 *__restrict__ heads) {
+    const int lane = threadIdx.x & 63;
+    const int64_t waves = (int64_t)gridDim.x * (blockDim.x >> 6);
+    for (int64_t c = blockIdx.x * (int64_t)(blockDim.x >> 6) + (threadIdx.x >> 6); c <= nchunk;
+         c += waves) {
+        int64_t p = c == nchunk ? nentry : c * (int64_t)len;
+        uint2 h = make_uint2(kHdrBit | kRootBit, 0u);
+        while (p < nentry) {
+            const uint2 w = p + lane < nentry ? st[p + lane] : make_uint2(0u, 0u);
+            const uint64_t m = __ballot((w.x & kHdrBit) != 0u);
+            if (m) {
+                const int l = __ffsll((unsigned long long)m) - 1;
+                p += l;
+                h = make_uint2((uint32_t)__shfl((int)w.x, l), (uint32_t)__shfl((int)w.y, l));
+                break;
+            }
+            p += 64;
         }
-        cs[c] = (uint32_t)p;
+        if (p > nentry) p = nentry;
+        if (lane == 0) {
+            cs[c] = (uint32_t)p;
+            heads[c] = h;
+        }
     }
 }
 
@@ -913,10 +951,10 @@ void radix_sort(uint64_t *&keys, uint32_t *&vals, uint64_t *&kalt, uint32_t *&va
 // continues the same row (no ROOT bit) forms one run of carries, (row, first
 // chunk, chunks).  One block per mode walks the chunks 1024 at a time; the
 // chunk that ends a sequence (its head opens a row, or continues another one)
-// writes the run before it, at its place in chunk order.
+// writes the run before it, at its place in chunk order.  The next 1024 heads
+// are loaded a step ahead.
 struct RunJob {
-    const uint2 *st;
-    const uint32_t *cs;
+    const uint2 *heads;
     uint32_t nchunk;
     uint32_t *shortr, *longr, *count;  // count: short runs, long runs
 };
@@ -927,24 +965,20 @@ __global__ __launch_bounds__(kRunBlock) void k_runs(const RunJob j0, const RunJo
     const RunJob &j = blockIdx.x == 0 ? j0 : blockIdx.x == 1 ? j1 : j2;
     __shared__ uint32_t s_pos[kRunBlock / 64], s_ns[kRunBlock / 64], s_nl[kRunBlock / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    auto head = [&](uint32_t c) {  // an empty chunk counts as opening a row
-        const uint32_t a = j.cs[c];
-        return a < j.cs[c + 1] ? j.st[a] : make_uint2(kHdrBit | kRootBit, 0u);
-    };
+    const uint2 none = make_uint2(kHdrBit | kRootBit, 0u);
+    auto head = [&](uint32_t c) { return c < j.nchunk ? j.heads[c] : none; };
     uint32_t open = 0, ns = 0, nl = 0;  // 1 + the last sequence start so far; runs written
+    uint2 hn = head(tid), gn = tid ? head(tid - 1) : none;  // this chunk's head, the one before
     for (uint32_t base = 0; base <= j.nchunk; base += kRunBlock) {
         const uint32_t c = base + tid;
         bool ends = false;
-        if (c < j.nchunk) {
-            const uint2 h = head(c);
-            ends = c == 0 || (h.x & kRootBit);
-            if (!ends) {
-                const uint2 g = head(c - 1);
-                ends = (g.x & kRootBit) || g.y != h.y;
-            }
-        } else if (c == j.nchunk) {
-            ends = true;
-        }
+        const uint2 hc = hn, gc = gn;
+        hn = head(c + kRunBlock);
+        gn = head(c + kRunBlock - 1);
+        if (c < j.nchunk)
+            ends = c == 0 || (hc.x & kRootBit) || (gc.x & kRootBit) || gc.y != hc.y;
+        else
+            ends = c == j.nchunk;
         const uint64_t m = __ballot(ends), below = m & ~(~0ull << lane);
         if (lane == 0) s_pos[wave] = m ? c + 64u - (uint32_t)__clzll((long long)m) : 0u;
         __syncthreads();
@@ -1067,14 +1101,22 @@ ModeCount count_mode(int64_t nrows, const C &c, int64_t n, Scratch &sc, hipStrea
     return k;
 }
 
-// Where the counts of count_mode lie: fibers, headers and empty rows as
-// (last offset, last count) pairs.
-void count_ends(const ModeCount &k, int64_t n, int64_t nrows, const uint32_t *(&a)[3],
-                const uint32_t *(&b)[3]) {
-    const int64_t nt = (n + kTile - 1) / kTile;
-    a[0] = k.fib_off + nt - 1, b[0] = k.nfib + nt - 1;
-    a[1] = k.hoff + nt - 1, b[1] = k.nhdr + nt - 1;
-    a[2] = k.rpos + nrows - 1, b[2] = k.mark + nrows - 1;
+// out[q] = *a[q] + *b[q] (b null: *a[q]): totals of scans and flags gathered
+// for one copy to the host (each copy costs the host 20 us)
+constexpr int kMostTotals = 9;
+struct Totals {
+    const uint32_t *a[kMostTotals], *b[kMostTotals];
+};
+__global__ void k_totals(const Totals t, int n, uint32_t *__restrict__ out) {
+    const int q = threadIdx.x;
+    if (q < n) out[q] = *t.a[q] + (t.b[q] ? *t.b[q] : 0u);
+}
+void read_totals(const Totals &t, int n, uint32_t *h, Scratch &sc, hipStream_t s) {
+    uint32_t *out = sc.alloc<uint32_t>(kMostTotals);
+    hipLaunchKernelGGL(k_totals, dim3(1), dim3(64), 0, s, t, n, out);
+    DF_LAUNCHED();
+    DF_HIP(hipMemcpyAsync(h, out, sizeof(uint32_t) * n, hipMemcpyDeviceToHost, s));
+    DF_HIP(hipStreamSynchronize(s));
 }
 
 // A mode of an empty tensor.
@@ -1128,10 +1170,11 @@ size_t size_mode(dfacto_tensor *t, int m, int64_t n, const ModeCount &k) {
 }
 
 // Mode m's flattening from its nonzeros (c, val), their counts and size_mode's
-// sizes (its run lists are left to finish_runs).
+// sizes; heads: its chunks' first headers (nchunk + 1), from which finish_runs
+// forms the run lists.
 template <class C>
 void emit_mode(dfacto_ctx *ctx, dfacto_tensor *t, int m, const C &c, const uint32_t *val,
-               int64_t n, const ModeCount &k, Scratch &sc) {
+               int64_t n, const ModeCount &k, uint2 *heads, Scratch &sc) {
     hipStream_t s = ctx->stream;
     ModeData &md = t->mode[m];
     const int64_t nrows = t->dims[md.root], nhdr = k.headers, L = md.nentry;
@@ -1168,21 +1211,21 @@ void emit_mode(dfacto_ctx *ctx, dfacto_tensor *t, int m, const C &c, const uint3
                        nrows, md.empty_rows);
     // work chunks
     md.chunk_start = tensor_alloc<uint32_t>(t, md.nchunk + 1);
-    hipLaunchKernelGGL(k_chunk_starts, dim3(grid_for(md.nchunk + 1)), dim3(kThreads), 0, s,
-                       md.stream, L, md.nchunk, md.chunk_len, md.chunk_start);
+    hipLaunchKernelGGL(k_chunk_starts, dim3(grid_for(md.nchunk + 1, kThreads / 64)),
+                       dim3(kThreads), 0, s, md.stream, L, md.nchunk, md.chunk_len,
+                       md.chunk_start, heads);
     DF_LAUNCHED();
 }
 
 // The run lists of all three modes (n > 0); waits.
-void finish_runs(dfacto_tensor *t, Scratch &sc, hipStream_t s) {
+void finish_runs(dfacto_tensor *t, uint2 *const (&heads)[3], Scratch &sc, hipStream_t s) {
     uint32_t *count = sc.alloc<uint32_t>(6);
     RunJob j[3];
     for (int m = 0; m < 3; ++m) {
         ModeData &md = t->mode[m];
         md.runs_short = tensor_alloc<uint32_t>(t, 3 * most_short(md.nchunk));
         md.runs_long = tensor_alloc<uint32_t>(t, 3 * most_long(md.nchunk));
-        j[m] = {md.stream, md.chunk_start, (uint32_t)md.nchunk,
-                md.runs_short, md.runs_long, count + 2 * m};
+        j[m] = {heads[m], (uint32_t)md.nchunk, md.runs_short, md.runs_long, count + 2 * m};
     }
     hipLaunchKernelGGL(k_runs, dim3(3), dim3(kRunBlock), 0, s, j[0], j[1], j[2]);
     DF_LAUNCHED();
@@ -1298,14 +1341,11 @@ int64_t count_distinct(const C &c, int64_t n, const uint32_t *flag, uint32_t **o
     hipLaunchKernelGGL(k_tile_distinct<C>, dim3((unsigned)nt), dim3(kThreads), 0, s, c, n, cnt);
     scan_exclusive<ScanSum>(cnt, *off, nt, s, &sc.mem);
     DF_LAUNCHED();
-    uint32_t h[3];
-    DF_HIP(hipMemcpyAsync(&h[0], flag, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-    DF_HIP(hipMemcpyAsync(&h[1], *off + nt - 1, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-    DF_HIP(hipMemcpyAsync(&h[2], cnt + nt - 1, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-    DF_HIP(hipStreamSynchronize(s));
+    uint32_t h[2];
+    read_totals(Totals{{flag, *off + nt - 1}, {nullptr, cnt + nt - 1}}, 2, h, sc, s);
     if (h[0] & 1u) throw Error{DFACTO_E_RANGE, "a coordinate is not below its dimension"};
     if (h[0] & 2u) throw Error{DFACTO_E_NUMERIC, "a tensor value is NaN or Inf"};
-    return (int64_t)h[1] + h[2];
+    return (int64_t)h[1];
 }
 
 // merge the duplicates of n sorted coordinates into nd distinct ones
@@ -1327,29 +1367,29 @@ void merge(const C &c, const float *v, int64_t n, const uint32_t *off, const Sto
 
 // one wait for the counts of several modes
 void read_counts(dfacto_tensor *t, ModeCount *k, const int *modes, int count, int64_t n,
-                 hipStream_t s) {
-    uint32_t h[18];
+                 Scratch &sc, hipStream_t s) {
+    const int64_t nt = (n + kTile - 1) / kTile;
+    Totals w{};
     for (int q = 0; q < count; ++q) {
-        const uint32_t *a[3], *b[3];
-        count_ends(k[q], n, t->dims[t->mode[modes[q]].root], a, b);
-        for (int x = 0; x < 3; ++x) {
-            DF_HIP(hipMemcpyAsync(&h[6 * q + 2 * x], a[x], sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-            DF_HIP(hipMemcpyAsync(&h[6 * q + 2 * x + 1], b[x], sizeof(uint32_t),
-                                  hipMemcpyDeviceToHost, s));
-        }
+        const int64_t nrows = t->dims[t->mode[modes[q]].root];
+        const uint32_t **a = w.a + 3 * q, **b = w.b + 3 * q;
+        a[0] = k[q].fib_off + nt - 1, b[0] = k[q].nfib + nt - 1;
+        a[1] = k[q].hoff + nt - 1, b[1] = k[q].nhdr + nt - 1;
+        a[2] = k[q].rpos + nrows - 1, b[2] = k[q].mark + nrows - 1;
     }
-    DF_HIP(hipStreamSynchronize(s));
+    uint32_t h[kMostTotals];
+    read_totals(w, 3 * count, h, sc, s);
     for (int q = 0; q < count; ++q) {
-        k[q].fibers = (int64_t)h[6 * q] + h[6 * q + 1];
-        k[q].headers = (int64_t)h[6 * q + 2] + h[6 * q + 3];
-        k[q].empty = (int64_t)h[6 * q + 4] + h[6 * q + 5];
+        k[q].fibers = h[3 * q];
+        k[q].headers = h[3 * q + 1];
+        k[q].empty = h[3 * q + 2];
     }
 }
 
 // indices of at most 64 bits together
 void build_packed(dfacto_ctx *ctx, dfacto_tensor *t, const uint32_t *d_i, const uint32_t *d_j,
                   const uint32_t *d_k, const float *d_val, int bI, int bJ, int bK,
-                  Scratch &sc) {
+                  Scratch &sc, uint2 *(&heads)[3]) {
     hipStream_t s = ctx->stream;
     const int64_t n = t->nnz;
     auto pairs = [&](int64_t m) { return PairBuf{sc.alloc<uint64_t>(m), sc.alloc<uint32_t>(m)}; };
@@ -1394,12 +1434,13 @@ void build_packed(dfacto_ctx *ctx, dfacto_tensor *t, const uint32_t *d_i, const 
     radix_sort(x[2], alt, nd, bJ, bJ + bK, sc, s, &x[1]);
     drop(alt);
     k[2] = count_mode(t->dims[2], coords(2, x[2]), nd, sc, s);
-    read_counts(t, k, modes, 3, nd, s);
+    read_counts(t, k, modes, 3, nd, sc, s);
     size_t bytes = 0;
     for (int m = 0; m < 3; ++m) bytes += size_mode(t, m, nd, k[m]);
     tensor_reserve(t, bytes);
     for (int m = 0; m < 3; ++m) {
-        emit_mode(ctx, t, m, coords(m, x[m]), x[m].val, nd, k[m], sc);
+        heads[m] = sc.alloc<uint2>(t->mode[m].nchunk + 1);
+        emit_mode(ctx, t, m, coords(m, x[m]), x[m].val, nd, k[m], heads[m], sc);
         drop(x[m]);
     }
 }
@@ -1407,7 +1448,7 @@ void build_packed(dfacto_ctx *ctx, dfacto_tensor *t, const uint32_t *d_i, const 
 // indices of more than 64 bits together
 void build_arrays(dfacto_ctx *ctx, dfacto_tensor *t, const uint32_t *d_i, const uint32_t *d_j,
                   const uint32_t *d_k, const float *d_val, int bI, int bJ, int bK,
-                  Scratch &sc) {
+                  Scratch &sc, uint2 *(&heads)[3]) {
     hipStream_t s = ctx->stream;
     const int64_t n = t->nnz;
     // coordinates and values are checked here and the outcome read with the
@@ -1473,9 +1514,10 @@ void build_arrays(dfacto_ctx *ctx, dfacto_tensor *t, const uint32_t *d_i, const 
         }
         Scratch scm(s, ctx->mem);
         ModeCount k = count_mode(t->dims[md.root], c, nd, scm, s);
-        read_counts(t, &k, &m, 1, nd, s);
+        read_counts(t, &k, &m, 1, nd, scm, s);
         (void)size_mode(t, m, nd, k);
-        emit_mode(ctx, t, m, c, (const uint32_t *)v, nd, k, scm);
+        heads[m] = sc.alloc<uint2>(md.nchunk + 1);
+        emit_mode(ctx, t, m, c, (const uint32_t *)v, nd, k, heads[m], scm);
     }
 }
 
@@ -1498,9 +1540,10 @@ void build_tensor(dfacto_ctx *ctx, dfacto_tensor *t, const uint32_t *d_i, const 
         return;
     }
     const int bI = bits_for(t->dims[0]), bJ = bits_for(t->dims[1]), bK = bits_for(t->dims[2]);
-    if (bI + bJ + bK <= 64) build_packed(ctx, t, d_i, d_j, d_k, d_val, bI, bJ, bK, sc);
-    else build_arrays(ctx, t, d_i, d_j, d_k, d_val, bI, bJ, bK, sc);
-    finish_runs(t, sc, s);
+    uint2 *heads[3];
+    if (bI + bJ + bK <= 64) build_packed(ctx, t, d_i, d_j, d_k, d_val, bI, bJ, bK, sc, heads);
+    else build_arrays(ctx, t, d_i, d_j, d_k, d_val, bI, bJ, bK, sc, heads);
+    finish_runs(t, heads, sc, s);
 }
 
 }  // namespace dfacto
