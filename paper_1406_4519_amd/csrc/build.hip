@@ -1287,7 +1287,8 @@ void build_row_ranges(dfacto_ctx *ctx, dfacto_tensor *t) {
         }
         t->row_range[m] = range;
     }
-    // rows longer than kJointSeg entries become segments of kJointSeg
+    // rows longer than kJointLight entries become at most kJointMaxSegs
+    // segments of kJointSeg entries or more
     std::vector<uint2> hr, seg[2];
     std::vector<uint4> heavy[2];
     for (int m = 0; m < 2; ++m) {
@@ -1298,11 +1299,13 @@ void build_row_ranges(dfacto_ctx *ctx, dfacto_tensor *t) {
         DF_HIP(hipStreamSynchronize(s));
         for (int64_t r = 0; r < rows; ++r) {
             const uint32_t b = hr[r].x, e = hr[r].y;
-            if (e - b <= (uint32_t)kJointSeg) continue;
-            heavy[m].push_back(make_uint4((uint32_t)r, (uint32_t)seg[m].size(),
-                                          (e - b + kJointSeg - 1) / kJointSeg, 0u));
-            for (uint32_t x = b; x < e; x += kJointSeg)
-                seg[m].push_back(make_uint2(x, std::min<uint32_t>(e, x + kJointSeg)));
+            if (e - b <= (uint32_t)kJointLight) continue;
+            const uint32_t len = std::max<uint32_t>(
+                kJointSeg, (e - b + kJointMaxSegs - 1) / kJointMaxSegs);
+            const uint32_t first = (uint32_t)seg[m].size(), n = (e - b + len - 1) / len;
+            heavy[m].push_back(make_uint4((uint32_t)r, first, n, 0u));
+            for (uint32_t x = 0; x < n; ++x)
+                seg[m].push_back(make_uint2(b + x * len, x + 1 < n ? b + (x + 1) * len : e));
         }
         t->nseg[m] = (int64_t)seg[m].size();
         t->nheavy[m] = (int64_t)heavy[m].size();

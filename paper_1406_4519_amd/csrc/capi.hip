@@ -800,12 +800,10 @@ dfacto_status dfacto_joint_als_iter(dfacto_ctx *ctx, const dfacto_tensor *X,
         }
         Small sw = small_ws(ctx, R);
         float *M = (float *)ws_get(ctx, dfacto_ctx::kM, sizeof(float) * (size_t)max_dim(X) * R);
-        // ones row, then the heavy rows' partial systems
+        // the heavy rows' partial systems
         const int64_t nseg = std::max(Y->nseg[0], Y->nseg[1]);
-        char *w = (char *)ws_get(ctx, dfacto_ctx::kJoint,
-                                 256 + sizeof(double) * (size_t)(nseg * (R * R + R) + 1));
-        void *one = ones_row(ctx, R, dtype, w);
-        double *part = (double *)(w + 256);
+        double *part = (double *)ws_get(ctx, dfacto_ctx::kJoint,
+                                        sizeof(double) * (joint_part_doubles(R, nseg) + 1));
         DF_HIP(hipMemsetAsync(sw.flag, 0, 4 * sizeof(int), ctx->stream));
         ensure_side(ctx);
         for (int n = 0; n < 3; ++n) {
@@ -836,13 +834,12 @@ dfacto_status dfacto_joint_als_iter(dfacto_ctx *ctx, const dfacto_tensor *X,
             if (mu > 0.0) launch_mttkrp(ctx, X, n, R, dtype, d_F[md.leaf], d_F[md.mid], M);
             DF_HIP(hipStreamWaitEvent(ctx->stream, ctx->ev_join, 0));
             if (n < 2) {
-                // users (n = 0): entries (1, item); items (n = 1): entries (user, 1);
                 // without the tensor term P^-1 = I / lam
                 const double *Pinv = mu > 0.0 ? sw.Hinv : nullptr;
                 const double ws = mu > 0.0 ? 1.0 / mu : 1.0 / lam;
-                launch_joint_rows(ctx, Y, n, X->dims[n], n == 0 ? one : d_F[0],
-                                  n == 0 ? d_F[1] : one, R, mu > 0.0 ? M : nullptr, sw.H[n], mu,
-                                  lam, Pinv, ws, sw.flag + 2, d_F[n], dtype, sw.flag, part);
+                launch_joint_rows(ctx, Y, n, X->dims[n], d_F[1 - n], R, mu > 0.0 ? M : nullptr,
+                                  sw.H[n], mu, lam, Pinv, ws, sw.flag + 2, d_F[n], dtype, sw.flag,
+                                  sw.flag + 3, part);
             } else if (mu > 0.0) {
                 launch_rowmap(ctx, M, X->dims[2], R, sw.Hinv, d_F[2], dtype);
             } else {

@@ -1201,27 +1201,473 @@ __global__ __launch_bounds__(kBlock) void k_sum_parts(const double *__restrict__
     if (threadIdx.x == 0) *out = acc;
 }
 
+// Raw 4-element runs (kept undecoded while in flight: half the registers of
+// doubles for FP32, a quarter for BF16).
+template <typename T>
+struct Run4;
+template <>
+struct Run4<float> {
+    float4 v;
+    __device__ __forceinline__ void load(const float *p) { v = *reinterpret_cast<const float4 *>(p); }
+    __device__ __forceinline__ void zero() { v = make_float4(0.f, 0.f, 0.f, 0.f); }
+    __device__ __forceinline__ double operator[](int i) const {
+        return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w;
+    }
+};
+template <>
+struct Run4<uint16_t> {
+    uint2 v;
+    __device__ __forceinline__ void load(const uint16_t *p) { v = *reinterpret_cast<const uint2 *>(p); }
+    __device__ __forceinline__ void zero() { v = make_uint2(0u, 0u); }
+    __device__ __forceinline__ double operator[](int i) const {
+        const uint32_t w = i < 2 ? v.x : v.y;
+        return __uint_as_float((i % 2 == 0) ? (w << 16) : (w & 0xFFFF0000u));
+    }
+};
+__device__ __forceinline__ void store4d(float *p, const double4v &a) {
+    *reinterpret_cast<float4 *>(p) = make_float4((float)a[0], (float)a[1], (float)a[2], (float)a[3]);
+}
+__device__ __forceinline__ void store4d(uint16_t *p, const double4v &a) {
+    uint2 w;
+    w.x = (uint32_t)f32_to_bf16((float)a[0]) | ((uint32_t)f32_to_bf16((float)a[1]) << 16);
+    w.y = (uint32_t)f32_to_bf16((float)a[2]) | ((uint32_t)f32_to_bf16((float)a[3]) << 16);
+    *reinterpret_cast<uint2 *>(p) = w;
+}
+
 // ---- joint matrix completion + tensor factorization ----------------------
-// One ALS row of the joint model per wave (R <= 32).  For the stored
-// entries of the row in a ratings stream (headers name the mid row,
-// nonzeros the leaf row and the rating y; the entry's vector is
-// v = F_mid[mid] * F_leaf[leaf], the other factor's row when the third
-// factor is a row of ones) the wave forms in FP64
-//   S = sum v^T v + mu H + lam I,   rhs = sum y v + mu M[row]
-// solves S x = rhs by Cholesky and writes out[row] = x in the factor dtype.
-// Register layout: lane (h, r) = (lane / 32, lane % 32) keeps
-// S[r][2k + h], k < 16, so both half-waves work on the row; entries, rows
-// and columns beyond R are zero.  Entries are taken 32 at a time (two lanes
-// load each entry's vector into LDS, all loads of a batch in flight
-// together), then the wave adds the batch's outer products in entry order.
-// Rows longer than kJointSeg entries are split into segments whose partial
-// (S, rhs) go to `part` and are summed in segment order by k_joint_heavy.
-// A row whose S fails the positive-definiteness test is written as zeros and
-// raises *flag.
+// The row systems of the joint ALS (R <= 32).  An entry of a row in a ratings
+// stream carries v = the other factor's row, named by the fiber's header
+// (by_mid) or by the nonzero itself (the third factor is a row of ones), and
+// the rating y; the row is x with
+//   (sum v^T v + mu H + lam I) x = sum y v + mu M[row],  all in FP64.
+//
+// Four rows a wave, every product on the matrix cores: v_mfma_f64_4x4x4 takes
+// four independent 4 x 4 x 4 products, one per row ("system").  Lane
+// (i, b, j) = (lane / 16, lane / 4 % 4, lane % 4) belongs to system b and
+// holds element (i, j) of each 4 x 4 block of its S; the same register is the
+// instruction's right operand, and as the left one stands for the block's
+// transpose.  Kept are the blocks on and above the diagonal (NB = 4 blocks a
+// side for R <= 16, 8 for R <= 32) and the right-hand side as one more block
+// column, used in its column j = 0.  Unknown i of block c is column
+// joint_col(c, i): lane j's 16-byte loads of a factor row are then whole
+// operands.  Columns beyond R are decoupled unit equations.
+//
+// What bounds it: FP64 issue -- 44 products of 16 cycles per four entries of
+// four rows, and 250 products with about as much scalar-pivot arithmetic per
+// solve of four -- at three waves a SIMD (168 registers).  One row a wave with
+// the columns broadcast through LDS was bound by LDS bandwidth, one 512-byte
+// broadcast read per multiply-add.  10M + 4M nonzeros, 400K users, 200K items,
+// R = 32, users and items together: rows 4594 -> 1206 us, split rows (segments
+// and their solves) 1476 -> 305 us.
 constexpr int kJointRM = 32;            // largest rank
-constexpr int kJointRP = kJointRM + 1;  // padded LDS row
-constexpr int kJointK = kJointRM / 2;   // columns of S per lane
-constexpr int kJointB = 32;             // entries per batch
+constexpr int kJointRP = kJointRM + 1;  // k_joint_small: padded LDS row
+constexpr int kJointK = kJointRM / 2;   // its columns of P^-1 per lane
+constexpr int kJointB = 32;             // its entries per batch
+constexpr int kJointWood = 7;           // its most nonzeros a row
+
+template <int NB>
+struct JointSys {
+    static constexpr int kS = NB * (NB + 1) / 2;
+    static constexpr int kAll = kS + NB;  // blocks of S, then of the right-hand side
+    double s[kS], b[NB];
+};
+
+template <int NB>
+__device__ __host__ constexpr int joint_at(int r, int c) {  // block (r, c), r <= c
+    return r * NB - r * (r - 1) / 2 + c - r;
+}
+
+__device__ __forceinline__ int joint_col(int c, int i) { return (c & 4) * 4 + 4 * i + (c & 3); }
+
+// the lane, opaque: what a lane's place decides is formed again for each
+// group of rows (kept across the loop it would spill)
+__device__ __forceinline__ int joint_lane() {
+    int l = threadIdx.x & 63;
+    asm volatile("" : "+v"(l));
+    return l;
+}
+
+__device__ __forceinline__ double mfma4(double a, double b, double c) {
+    return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
+}
+
+template <int ctrl>
+__device__ __forceinline__ double dpp(double v) {
+    const long long x = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(x & 0xffffffffll), ctrl, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(x >> 32), ctrl, 0xf, 0xf, true);
+    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+}
+// lane t of each quad's v in all four of its lanes
+template <int t>
+__device__ __forceinline__ double quad_bcast(double v) {
+    return dpp<t * 0x55>(v);
+}
+// the four systems' sum, in all of them (rotations within 16 lanes)
+__device__ __forceinline__ double systems_sum(double v) {
+    v += dpp<0x128>(v);
+    return v + dpp<0x124>(v);
+}
+
+// P = mu H + lam I in a workgroup's LDS (16 elements a block), unit equations beyond R
+template <int NB>
+__device__ __forceinline__ void joint_base(double *P, const double *__restrict__ H, int R, double mu,
+                                           double lam) {
+    int r = 0, c = 0;
+    for (int q = threadIdx.x >> 4, at = 0; q < JointSys<NB>::kS; q += 4) {
+        for (; at < q; ++at)
+            if (++c == NB) c = ++r;
+        const int row = joint_col(r, (threadIdx.x >> 2) & 3), col = joint_col(c, threadIdx.x & 3);
+        double v = row == col ? 1.0 : 0.0;
+        if (row < R && col < R) v = mu * H[row * R + col] + (row == col ? lam : 0.0);
+        P[q * 16 + (threadIdx.x & 15)] = v;
+    }
+    __syncthreads();
+}
+
+// S = P
+template <int NB>
+__device__ __forceinline__ void joint_start(JointSys<NB> &S, const double *P, int l) {
+    const int at = (l >> 4) * 4 + (l & 3);
+    asm volatile("" ::: "memory");  // read here, not kept in registers
+#pragma unroll
+    for (int q = 0; q < JointSys<NB>::kS; ++q) S.s[q] = P[q * 16 + at];
+}
+
+// b = mu M[row] (zero without M, or for a system without a row)
+template <int NB>
+__device__ __forceinline__ void joint_rhs(JointSys<NB> &S, const float *__restrict__ M, int64_t row,
+                                          int R, double mu, bool mine, int l) {
+    const int i = l >> 4, j = l & 3;
+#pragma unroll
+    for (int c = 0; c < NB; ++c) {
+        const int col = joint_col(c, i);
+        const double m = M ? mu * (double)M[row * R + min(col, R - 1)] : 0.0;
+        S.b[c] = mine && j == 0 && col < R ? m : 0.0;
+    }
+}
+
+// the 16 bits of my system's lanes in a ballot, in the order 4 i + j
+__device__ __forceinline__ uint32_t joint_mask(uint64_t m, int b) {
+    const uint64_t y = m >> (4 * b);
+    return (uint32_t)((y & 0xFull) | ((y >> 12) & 0xF0ull) | ((y >> 24) & 0xF00ull) |
+                      ((y >> 36) & 0xF000ull));
+}
+
+// Adds the entries [e, e1) of each system's range (per system; empty ranges
+// allowed): S += v^T v, rhs += y v.  `mid` is the index named by the header
+// open at e.  Returns the system's number of nonzeros.  A step takes 16 entries per
+// system, one a lane, closes up the nonzeros (a permutation within the
+// system's 16 lanes) and adds them four at a time.
+template <typename T, int NB, bool VEC>
+__device__ __forceinline__ uint32_t joint_gather(const uint2 *__restrict__ st, uint32_t e,
+                                                 uint32_t e1, uint32_t mid,
+                                                 const T *__restrict__ F, bool by_mid, int R,
+                                                 JointSys<NB> &S, int l) {
+    const int i = l >> 4, b = (l >> 2) & 3, j = l & 3, pos = 4 * i + j;
+    uint32_t total = 0, n = 0, most = 0;  // `most`: n's maximum over the four systems
+    int qi = 0, qy = 0;
+    e += (uint32_t)pos;
+    // loads are clamped, not branched around (the stream has an entry, F a row)
+    uint2 w = st[e < e1 ? e : 0];
+    // one loop around the products with its one exit at the end (a nest, or an
+    // exit at the refill, would keep S twice)
+    uint32_t t = 0;
+    bool more = false;
+    do {
+        if (4 * t >= most) {
+            const bool in = e < e1;
+            const uint64_t hb = __ballot(in && (w.x & kHdrBit));
+            const uint64_t nb = __ballot(in && !(w.x & kHdrBit));
+            const uint32_t hm = joint_mask(hb, b), nm = joint_mask(nb, b);
+            uint32_t idx = w.x & kIdxMask;
+            if (by_mid) {
+                const uint32_t upto = hm & ((2u << pos) - 1u);
+                const int at = 31 - __clz((int)(upto | 1u)), last = 31 - __clz((int)(hm | 1u));
+                const uint32_t own =
+                    (uint32_t)__shfl((int)idx, (at >> 2) * 16 + 4 * b + (at & 3));
+                const uint32_t end =
+                    (uint32_t)__shfl((int)idx, (last >> 2) * 16 + 4 * b + (last & 3));
+                idx = upto ? own : mid;
+                if (hm) mid = end;
+            }
+            // nonzeros first, in stream order, the rest behind them
+            n = (uint32_t)__popc(nm);
+            const uint32_t below = (1u << pos) - 1u;
+            const uint32_t slot = ((nm >> pos) & 1u) ? (uint32_t)__popc(nm & below)
+                                                     : n + (uint32_t)__popc(~nm & below);
+            const int to = (int)(((slot >> 2) * 16 + 4 * (uint32_t)b + (slot & 3)) * 4);
+            qi = __builtin_amdgcn_ds_permute(to, (int)idx);
+            qy = __builtin_amdgcn_ds_permute(to, (int)w.y);
+            total += n;
+            most = 0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                most = max(most, (uint32_t)__popcll(nb & (0x000F000F000F000Full << (4 * q))));
+            t = 0;
+            e += 16;
+            more = __ballot(e < e1) != 0;
+            w = st[e < e1 ? e : 0];  // the next step's, in flight meanwhile
+        }
+        {
+            const int src = 16 * (int)t + 4 * b + i;  // slot 4 t + i
+            const uint32_t at = (uint32_t)__shfl(qi, src), yb = (uint32_t)__shfl(qy, src);
+            const bool ok = 4 * t + (uint32_t)i < n;
+            const T *f = F + (int64_t)(ok ? at : 0u) * R;
+            double v[NB];
+            if (VEC) {
+                Run4<T> run[NB / 4];
+#pragma unroll
+                for (int q = 0; q < NB / 4; ++q) run[q].load(f + min(16 * q + 4 * j, R - 4));
+#pragma unroll
+                for (int c = 0; c < NB; ++c)
+                    v[c] = ok && joint_col(c, j) < R ? run[c / 4][c % 4] : 0.0;
+            } else {
+#pragma unroll
+                for (int c = 0; c < NB; ++c) {
+                    const double x = ld<T>(f, min(joint_col(c, j), R - 1));
+                    v[c] = ok && joint_col(c, j) < R ? x : 0.0;
+                }
+            }
+            const double y = ok && j == 0 ? (double)__uint_as_float(yb) : 0.0;
+#pragma unroll
+            for (int r = 0; r < NB; ++r) {
+#pragma unroll
+                for (int c = r; c < NB; ++c)
+                    S.s[joint_at<NB>(r, c)] = mfma4(v[r], v[c], S.s[joint_at<NB>(r, c)]);
+                S.b[r] = mfma4(v[r], y, S.b[r]);
+            }
+        }
+        ++t;
+    } while (4 * t < most || more);
+    return total;
+}
+
+// 1 / sqrt(d), d > 0 and normal: the estimate and one third-order step
+// (r + r e (1/2 + 3/8 e), e = 1 - d r^2: past 2^-26 this leaves the rounding)
+__device__ __forceinline__ double joint_rsqrt(double d) {
+    const double r = __builtin_amdgcn_rsq(d);
+    const double e = fma(-d * r, r, 1.0);
+    return fma(r * e, fma(e, 0.375, 0.5), r);
+}
+
+// one pivot of a diagonal block: a's rows below are eliminated, u keeps
+// the inverse unit factor's transpose and ds the pivots' inverse roots
+template <int t>
+__device__ __forceinline__ void joint_pivot(double &a, double &u, double &ds, bool &ok, bool pad,
+                                            double tol, int i, int j) {
+    const double row = mfma4(i == t ? 1.0 : 0.0, a, 0.0);  // a[t][j] in every i
+    const double d = quad_bcast<t>(row);                    // the Schur-complement pivot
+    ok = ok & (pad | (d > tol));  // (no branches)
+    const double inv = joint_rsqrt(d);
+    ds = j == t ? inv : ds;
+    if (t < 3) {
+        const double m = j > t ? row * (inv * inv) : 0.0;
+        const double ca = quad_bcast<t>(a), cu = quad_bcast<t>(u);
+        a = fma(-ca, m, a);
+        u = fma(-cu, m, u);
+    }
+}
+
+// S x = b for the wave's four systems; x comes back in S.b.  Blocked Cholesky
+// S = U^T U with the pivot test d > R eps max diag(S); the inverse of each
+// diagonal block of U takes the block's place.  Returns whether the system
+// passed (its x is meaningless otherwise; the other systems don't see it).
+template <int NB>
+__device__ __forceinline__ bool joint_solve(JointSys<NB> &S, int R, int l) {
+    const int i = l >> 4, j = l & 3;
+    double dm = 0.0;
+#pragma unroll
+    for (int c = 0; c < NB; ++c)
+        if (i == j && joint_col(c, j) < R) dm = fmax(dm, S.s[joint_at<NB>(c, c)]);
+#pragma unroll
+    for (int o = 1; o < 64; o = o == 2 ? 16 : 2 * o) dm = fmax(dm, __shfl_xor(dm, o, 64));
+    const double tol = (double)R * DBL_EPSILON * dm;
+    bool ok = dm > 0.0;
+    const double eye = i == j ? 1.0 : 0.0;
+#pragma unroll
+    for (int p = 0; p < NB; ++p) {
+        double a = S.s[joint_at<NB>(p, p)], u = eye, ds = 0.0;
+        joint_pivot<0>(a, u, ds, ok, joint_col(p, 0) >= R, tol, i, j);
+        joint_pivot<1>(a, u, ds, ok, joint_col(p, 1) >= R, tol, i, j);
+        joint_pivot<2>(a, u, ds, ok, joint_col(p, 2) >= R, tol, i, j);
+        joint_pivot<3>(a, u, ds, ok, joint_col(p, 3) >= R, tol, i, j);
+        u *= ds;
+        S.s[joint_at<NB>(p, p)] = u;
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int c = p + 1; c < NB; ++c)
+            S.s[joint_at<NB>(p, c)] = mfma4(u, S.s[joint_at<NB>(p, c)], 0.0);
+        S.b[p] = mfma4(u, S.b[p], 0.0);
+#pragma unroll
+        for (int r = p + 1; r < NB; ++r) {
+            const double nu = -S.s[joint_at<NB>(p, r)];
+#pragma unroll
+            for (int c = r; c < NB; ++c)
+                S.s[joint_at<NB>(r, c)] =
+                    mfma4(nu, S.s[joint_at<NB>(p, c)], S.s[joint_at<NB>(r, c)]);
+            S.b[r] = mfma4(nu, S.b[p], S.b[r]);
+        }
+    }
+    // U x = y, a product with the unit block transposing each left operand
+#pragma unroll
+    for (int p = NB - 1; p >= 0; --p) {
+        S.b[p] = mfma4(mfma4(S.s[joint_at<NB>(p, p)], eye, 0.0), S.b[p], 0.0);
+#pragma unroll
+        for (int r = 0; r < p; ++r)
+            S.b[r] = mfma4(-mfma4(S.s[joint_at<NB>(r, p)], eye, 0.0), S.b[p], S.b[r]);
+        __builtin_amdgcn_sched_barrier(0);  // few transposes in flight
+    }
+    return ok;
+}
+
+// out[row] = x (zeros when the system failed), by the lanes j = 0
+template <typename T, int NB>
+__device__ __forceinline__ void joint_store(const JointSys<NB> &S, bool ok, int64_t row, int R,
+                                            bool vec, T *__restrict__ out, int l) {
+    const int i = l >> 4;
+    T *o = out + row * R;
+#pragma unroll
+    for (int q = 0; q < NB / 4; ++q) {
+        const int col = 16 * q + 4 * i;
+        double4v x;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) x[c] = ok ? S.b[4 * q + c] : 0.0;
+        if (vec) {
+            if (col < R) store4d(o + col, x);
+        } else {
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (col + c < R) st_out<T>(o, col + c, x[c]);
+        }
+    }
+}
+
+// every row of at most kJointLight entries, four a wave (persistent grid: a
+// workgroup forms P once).  A row of at most kJointWood nonzeros in one batch
+// that fails the test raises *need instead of *flag: k_joint_small decides.
+template <typename T, int NB, bool VEC>
+__global__ __launch_bounds__(64, 3) void k_joint_rows(
+    const uint2 *__restrict__ st, const uint2 *__restrict__ range, int64_t nrows,
+    const T *__restrict__ F, bool by_mid, int R, const float *__restrict__ M,
+    const double *__restrict__ H, double mu, double lam, T *__restrict__ out,
+    int *__restrict__ flag, int *__restrict__ need) {
+    using Sys = JointSys<NB>;
+    __shared__ double P[Sys::kS * 16];
+    joint_base<NB>(P, H, R, mu, lam);
+    for (int64_t g = blockIdx.x; 4 * g < nrows; g += gridDim.x) {
+        const int l = joint_lane(), i = l >> 4, b = (l >> 2) & 3, j = l & 3;
+        const int64_t row = 4 * g + b;
+        uint2 rg = row < nrows ? range[row] : make_uint2(0u, 0u);
+        const bool mine = row < nrows && rg.y - rg.x <= (uint32_t)kJointLight;
+        if (!mine) rg = make_uint2(0u, 0u);
+        Sys S;
+        joint_start<NB>(S, P, l);
+        joint_rhs<NB>(S, M, mine ? row : 0, R, mu, mine, l);
+        const uint32_t n = joint_gather<T, NB, VEC>(st, rg.x, rg.y, 0u, F, by_mid, R, S, l);
+        const bool ok = joint_solve<NB>(S, R, l);
+        if (mine && j == 0) {
+            joint_store<T, NB>(S, ok, row, R, VEC, out, l);
+            if (!ok && i == 0)
+                atomicOr(rg.y - rg.x <= (uint32_t)kJointB && n <= (uint32_t)kJointWood ? need : flag,
+                         1);
+        }
+    }
+}
+
+// One segment of a heavy row: its entries over the 16 systems of four waves,
+// added up in a fixed order to one partial system (kAll blocks of 16).
+template <typename T, int NB, bool VEC>
+__global__ __launch_bounds__(256, 3) void k_joint_segments(
+    const uint2 *__restrict__ st, const uint2 *__restrict__ seg, int64_t nseg,
+    const T *__restrict__ F, bool by_mid, int R, double *__restrict__ part) {
+    using Sys = JointSys<NB>;
+    __shared__ double red[4][Sys::kAll * 16];
+    const int l = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int i = l >> 4, b = (l >> 2) & 3, j = l & 3, pos = 4 * i + j;
+    for (int64_t q = blockIdx.x; q < nseg; q += gridDim.x) {
+        const uint2 sg = seg[q];
+        const uint32_t len = (((sg.y - sg.x + 15) / 16 + 15) / 16) * 16;  // per system
+        const uint32_t e0 = min(sg.y, sg.x + (uint32_t)(4 * wv + b) * len);
+        const uint32_t e1 = min(sg.y, e0 + len);
+        // the header open at e0 is at most one fiber before it, and the row's
+        // first entry is a header
+        uint32_t mid = 0;
+        if (by_mid) {
+            bool open = e0 < e1 && !(st[e0].x & kHdrBit);
+            for (uint32_t back = 1; __ballot(open) != 0; back += 16) {
+                const uint32_t d = back + (uint32_t)pos;
+                const uint2 w = open && d <= e0 ? st[e0 - d] : make_uint2(0u, 0u);
+                const uint32_t hm = joint_mask(__ballot((w.x & kHdrBit) != 0), b);
+                const int at = __ffs((int)(hm | 0x10000u)) - 1;  // the nearest
+                const uint32_t m =
+                    (uint32_t)__shfl((int)(w.x & kIdxMask), ((at >> 2) & 3) * 16 + 4 * b + (at & 3));
+                if (open && hm) {
+                    mid = m;
+                    open = false;
+                }
+                if (back + 16 > e0) open = false;
+            }
+        }
+        Sys S;
+#pragma unroll
+        for (int x = 0; x < Sys::kS; ++x) S.s[x] = 0.0;
+#pragma unroll
+        for (int x = 0; x < NB; ++x) S.b[x] = 0.0;
+        joint_gather<T, NB, VEC>(st, e0, e1, mid, F, by_mid, R, S, l);
+#pragma unroll
+        for (int x = 0; x < Sys::kAll; ++x) {
+            double v = x < Sys::kS ? S.s[x < Sys::kS ? x : 0] : S.b[x < Sys::kS ? 0 : x - Sys::kS];
+            v = systems_sum(v);
+            if (b == 0) red[wv][x * 16 + pos] = v;
+        }
+        __syncthreads();
+        for (int x = threadIdx.x; x < Sys::kAll * 16; x += 256)
+            part[q * (Sys::kAll * 16) + x] = ((red[0][x] + red[1][x]) + red[2][x]) + red[3][x];
+        __syncthreads();
+    }
+}
+
+// heavy rows, four a wave: the sum of a row's partial systems in segment
+// order, solved
+template <typename T, int NB>
+__global__ __launch_bounds__(64, 2) void k_joint_heavy(const uint4 *__restrict__ heavy,
+                                                    int64_t nheavy, int R, bool vec,
+                                                    const double *__restrict__ part,
+                                                    const float *__restrict__ M,
+                                                    const double *__restrict__ H, double mu,
+                                                    double lam, T *__restrict__ out,
+                                                    int *__restrict__ flag) {
+    using Sys = JointSys<NB>;
+    __shared__ double P[Sys::kS * 16];
+    joint_base<NB>(P, H, R, mu, lam);
+    for (int64_t g = blockIdx.x; 4 * g < nheavy; g += gridDim.x) {
+        const int l = joint_lane(), i = l >> 4, b = (l >> 2) & 3, j = l & 3;
+        const bool mine = 4 * g + b < nheavy;
+        // (row, first segment, segments, 0)
+        const uint4 hv = mine ? heavy[4 * g + b] : make_uint4(0u, 0u, 0u, 0u);
+        const int64_t row = (int64_t)hv.x;
+        Sys S;
+        joint_start<NB>(S, P, l);
+        joint_rhs<NB>(S, M, row, R, mu, mine, l);
+        for (uint32_t q = hv.y; q < hv.y + hv.z; ++q) {
+            const double *pt = part + (int64_t)q * (Sys::kAll * 16) + 4 * i + j;
+            double v[Sys::kAll];  // all loads in flight
+#pragma unroll
+            for (int x = 0; x < Sys::kAll; ++x) v[x] = pt[x * 16];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int x = 0; x < Sys::kS; ++x) S.s[x] += v[x];
+#pragma unroll
+            for (int x = 0; x < NB; ++x) S.b[x] += v[Sys::kS + x];
+        }
+        const bool ok = joint_solve<NB>(S, R, l);
+        if (mine && j == 0) {
+            joint_store<T, NB>(S, ok, row, R, vec, out, l);
+            if (!ok && i == 0) atomicOr(flag, 1);
+        }
+    }
+}
 
 // lane `src`'s v (src uniform) in every lane
 __device__ __forceinline__ double lane_bcast(double v, int src) {
@@ -1231,25 +1677,13 @@ __device__ __forceinline__ double lane_bcast(double v, int src) {
     return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
-// lane (h, r): p[k] = (mu H + lam I)[r][2k + h] (zero outside R x R)
-__device__ __forceinline__ void joint_shift(const double *__restrict__ H, int R, double mu,
-                                            double lam, double (&p)[kJointK]) {
-    const int h = threadIdx.x >> 5, r = threadIdx.x & 31;
-#pragma unroll
-    for (int k = 0; k < kJointK; ++k) {
-        const int q = 2 * k + h;
-        p[k] = (r < R && q < R) ? mu * H[r * R + q] + (q == r ? lam : 0.0) : 0.0;
-    }
-}
-
 // One batch [b, min(b + 32, e1)) of a ratings stream: the nonzeros'
 // vectors go, compacted in stream order, to rows 0 .. n-1 of V (columns
-// beyond R zero) and their ratings to Yb; returns n.  cur_mid is the mid row
-// of the fiber open at b and comes back as the one open at the batch's end.
+// beyond R zero) and their ratings to Yb; returns n.  A header opens the batch.
 template <typename T>
 __device__ int joint_load_batch(const uint2 *__restrict__ st, uint32_t b, uint32_t e1,
-                                const T *__restrict__ Fmid, const T *__restrict__ Fleaf, int R,
-                                uint32_t &cur_mid, double *V, double *Yb) {
+                                const T *__restrict__ F, bool by_mid, int R, double *V,
+                                double *Yb) {
     const int h = threadIdx.x >> 5, t = threadIdx.x & 31;
     // entry t of the batch in lanes t and t + 32
     const uint32_t e = b + (uint32_t)t;
@@ -1261,66 +1695,19 @@ __device__ int joint_load_batch(const uint2 *__restrict__ st, uint32_t b, uint32
     const uint64_t nm = __ballot(nz) & 0xffffffffull;
     const uint64_t upto = hm & ((2ull << t) - 1ull);
     const uint32_t midx = w.x & kIdxMask;
-    const uint32_t lastm = hm ? (uint32_t)__shfl((int)midx, 63 - __clzll((long long)hm)) : 0u;
-    const uint32_t srcm = upto ? (uint32_t)__shfl((int)midx, 63 - __clzll((long long)upto)) : 0u;
-    const uint32_t my_mid = upto ? srcm : cur_mid;
-    if (hm) cur_mid = lastm;
+    const uint32_t mid = (uint32_t)__shfl((int)midx, upto ? 63 - __clzll((long long)upto) : 0);
     if (nz) {
         const int slot = __popcll(nm & ((1ull << t) - 1ull));
-        const T *pm = Fmid + (int64_t)my_mid * R;
-        const T *pl = Fleaf + (int64_t)w.x * R;
+        const T *f = F + (int64_t)(by_mid ? mid : w.x) * R;
 #pragma unroll
         for (int k = 0; k < kJointK; ++k) {
             const int q = 2 * k + h;
-            V[slot * kJointRP + q] = q < R ? ld<T>(pm, q) * ld<T>(pl, q) : 0.0;
+            V[slot * kJointRP + q] = q < R ? ld<T>(f, q) : 0.0;
         }
         if (h == 0) Yb[slot] = (double)__uint_as_float(w.y);
     }
     __syncthreads();
     return __popcll(nm);
-}
-
-// c[k] += sum_u v_u[r] v_u[2k + h], rhs += sum_u y_u v_u[r] over the n
-// loaded entries, in order
-__device__ __forceinline__ void joint_add_batch(int n, double (&c)[kJointK], double &rhs,
-                                                const double *V, const double *Yb) {
-    const int h = threadIdx.x >> 5, t = threadIdx.x & 31;
-    for (int u = 0; u < n; ++u) {
-        const double vr = V[u * kJointRP + t];  // v[r]: zero for r >= R
-        rhs = fma(Yb[u], vr, rhs);
-#pragma unroll
-        for (int k = 0; k < kJointK; ++k) c[k] = fma(V[u * kJointRP + 2 * k + h], vr, c[k]);
-    }
-    __syncthreads();
-}
-
-// c[k] += sum over the entries [e0, e1) of v[r] v[2k + h]; rhs += sum y v[r]
-template <typename T, bool kSegment>
-__device__ void joint_accumulate(const uint2 *__restrict__ st, uint32_t e0, uint32_t e1,
-                                 const T *__restrict__ Fmid, const T *__restrict__ Fleaf, int R,
-                                 double (&c)[kJointK], double &rhs, double *V, double *Yb) {
-    const int l = threadIdx.x;
-    // a segment may start inside a fiber: the fiber's header is at most one
-    // fiber (<= kFiberCap nonzeros) before e0, and the row's first entry is a
-    // header (a whole row starts with one)
-    uint32_t cur_mid = 0;
-    if (kSegment && !(st[e0].x & kHdrBit)) {
-        for (uint32_t back = 0; back < e0; back += 64) {
-            const uint32_t e = e0 - 1 - back - (uint32_t)l;  // e0 - 1 - back - l >= row start here
-            const bool in = back + (uint32_t)l < e0;
-            const uint2 w = in ? st[e] : make_uint2(0u, 0u);
-            const uint64_t hb = __ballot(in && (w.x & kHdrBit));
-            if (hb) {
-                const int src = __ffsll((unsigned long long)hb) - 1;  // the nearest header
-                cur_mid = (uint32_t)__shfl((int)(w.x & kIdxMask), src);
-                break;
-            }
-        }
-    }
-    for (uint32_t b = e0; b < e1; b += kJointB) {
-        const int n = joint_load_batch<T>(st, b, e1, Fmid, Fleaf, R, cur_mid, V, Yb);
-        joint_add_batch(n, c, rhs, V, Yb);
-    }
 }
 
 // A row of at most kJointWood entries (vectors v_e in rows of V, ratings in
@@ -1333,12 +1720,8 @@ __device__ void joint_accumulate(const uint2 *__restrict__ st, uint32_t e0, uint
 // Gauss-Jordan without pivoting, lane (e, f) = e * 8 + f holding K[e][f]
 // and lane (e, n) holding t[e].  U (kJointRM rows of kJointRP doubles, apart
 // from V's first n rows) holds u_e and z; Bb (32 doubles) carries b.
-constexpr int kJointWood = 7;
-
-// (not inlined: inside the rows kernel's loop it would cost a wave per SIMD
-// of registers)
 template <typename T>
-__device__ __noinline__ void joint_woodbury(int n, const double *V, const double *Yb, double mu, double m,
+__device__ void joint_woodbury(int n, const double *V, const double *Yb, double mu, double m,
                                const double *__restrict__ Pinv, double ws, int R, int64_t row,
                                T *__restrict__ out, double *U, double *Bb) {
     const int l = threadIdx.x, h = l >> 5, r = l & 31;
@@ -1389,185 +1772,36 @@ __device__ __noinline__ void joint_woodbury(int n, const double *V, const double
     __syncthreads();  // U, V and Bb are free again
 }
 
-// S = c + p (p = mu H + lam I in the same layout); b = rhs (lane (h, r)
-// holds rhs[r]).  Cholesky S = L L^T with
-// the pivot test d_j > R eps max diag(S), forward substitution folded into
-// the factorization, then L^T x = y after one transpose of L through LDS;
-// out[row] = x.  Lc (2 x 32 doubles) carries the current column of L,
-// Tl (32 x kJointRP doubles) the transpose.
+// Short rows whose own system is too close to singular for the pivot test
+// although P is not (a tiny lam and few ratings): all short rows once more by
+// the Woodbury identity, from P^-1.  Does nothing unless a short row raised
+// *need; without a valid P^-1 (*pflag != 0) such a row is a failure.
 template <typename T>
-__device__ void joint_solve_store(double (&c)[kJointK], double b, const double (&p)[kJointK],
-                                  int64_t row, int R, T *__restrict__ out,
-                                  int *__restrict__ flag, double *Lc, double *Tl) {
-    const int l = threadIdx.x, h = l >> 5, r = l & 31;
-    double dl = 0.0;
-#pragma unroll
-    for (int k = 0; k < kJointK; ++k) {
-        const int q = 2 * k + h;
-        c[k] += p[k];
-        if (q == r) dl = c[k];
+__global__ __launch_bounds__(64) void k_joint_small(const uint2 *__restrict__ st,
+                                                    const uint2 *__restrict__ range, int64_t nrows,
+                                                    const T *__restrict__ F, bool by_mid, int R,
+                                                    const float *__restrict__ M, double mu,
+                                                    const double *__restrict__ Pinv, double ws,
+                                                    const int *__restrict__ pflag,
+                                                    T *__restrict__ out, int *__restrict__ flag,
+                                                    const int *__restrict__ need) {
+    __shared__ double V[kJointB * kJointRP], Yb[kJointB], Bb[32];
+    if (*need == 0) return;
+    if (Pinv && *pflag != 0) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) atomicOr(flag, 1);
+        return;
     }
-    double dm = dl;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) dm = fmax(dm, __shfl_xor(dm, o, 64));
-    const double tol = (double)R * DBL_EPSILON * dm;
-    bool ok = dm > 0.0;
-    double myinv = 0.0;  // 1 / L[r][r]
-    // fully unrolled (no early exit): every index into c is a constant
-#pragma unroll
-    for (int j = 0; j < kJointRM; ++j) {
-        const int jh = j & 1, jk = j >> 1;
-        const double d = lane_bcast(c[jk], jh * 32 + j);  // the Schur-complement pivot
-        if (j < R && ok) ok = d > tol;
-        if (j < R && ok) {
-            const double inv = rsqrt(d);
-            double *lc = Lc + jh * 32;  // two buffers: no barrier before the next write
-            if (h == jh) lc[r] = r > j ? c[jk] * inv : 0.0;
-            const double yj = lane_bcast(b, j) * inv;
-            if (r == j) myinv = inv;
-            __syncthreads();
-            const double lr = lc[r];  // L[r][j], zero for r <= j
-            if (h == jh && r > j) c[jk] = lr;
-            b = r == j ? yj : fma(-lr, yj, b);
-            double lk[kJointK];  // all reads of the column in flight together
-#pragma unroll
-            for (int k = jk; k < kJointK; ++k) lk[k] = lc[2 * k + h];
-#pragma unroll
-            for (int k = jk; k < kJointK; ++k) c[k] = fma(-lr, lk[k], c[k]);
-        }
-    }
-    if (ok) {
-        // L^T x = y: lane (h, r) keeps lt[k] = L[2k + h][r] and in acc the
-        // sum of L[j][r] x_j over the solved j of its parity h, so
-        // x_j = (y_j - acc(0, j) - acc(1, j)) / L[j][j]
-#pragma unroll
-        for (int k = 0; k < kJointK; ++k) Tl[r * kJointRP + 2 * k + h] = c[k];
-        __syncthreads();
-        double lt[kJointK];
-#pragma unroll
-        for (int k = 0; k < kJointK; ++k) lt[k] = Tl[(2 * k + h) * kJointRP + r];
-        double acc = 0.0, x = 0.0;
-#pragma unroll
-        for (int j = kJointRM - 1; j >= 0; --j) {
-            if (j < R) {
-                const double xj = (lane_bcast(b - acc, j) - lane_bcast(acc, 32 + j)) *
-                                  lane_bcast(myinv, j);
-                if (r == j) x = xj;
-                if (h == (j & 1) && r < j) acc = fma(lt[j >> 1], xj, acc);
-            }
-        }
-        b = x;
-    }
-    __syncthreads();  // Tl and Lc are free again
-    if (h == 0 && r < R) st_out<T>(out, row * R + r, ok ? b : 0.0);
-    if (!ok && l == 0) atomicOr(flag, 1);
-}
-
-// every row of at most kJointSeg entries: accumulate, solve, store
-// (persistent grid: each workgroup forms mu H + lam I once and walks rows)
-// Rows whose stream range fits one batch and holds at most kJointWood
-// entries take joint_woodbury when P^-1 is valid (Pinv null, or its solve
-// reported success in *pflag == 0).
-template <typename T>
-__global__ __launch_bounds__(64) void k_joint_rows(const uint2 *__restrict__ st,
-                                                   const uint2 *__restrict__ range, int64_t nrows,
-                                                   const T *__restrict__ Fmid,
-                                                   const T *__restrict__ Fleaf, int R,
-                                                   const float *__restrict__ M,
-                                                   const double *__restrict__ H, double mu,
-                                                   double lam, const double *__restrict__ Pinv,
-                                                   double ws, const int *__restrict__ pflag,
-                                                   T *__restrict__ out, int *__restrict__ flag) {
-    __shared__ double V[kJointB * kJointRP], Yb[kJointB], Lc[2 * 32];
     const int r = threadIdx.x & 31;
-    double p[kJointK];
-    joint_shift(H, R, mu, lam, p);
-    const bool wood = !Pinv || *pflag == 0;
-    uint2 next = blockIdx.x < nrows ? range[blockIdx.x] : make_uint2(0u, 0u);
     for (int64_t row = blockIdx.x; row < nrows; row += gridDim.x) {
-        const uint2 rg = next;  // the next row's range is read while this one is solved
-        if (row + gridDim.x < nrows) next = range[row + gridDim.x];
-        if (rg.y - rg.x > (uint32_t)kJointSeg) continue;  // a heavy row: segments below
+        const uint2 rg = range[row];
+        if (rg.y - rg.x > (uint32_t)kJointB) continue;
+        const int n = rg.y > rg.x ? joint_load_batch<T>(st, rg.x, rg.y, F, by_mid, R, V, Yb) : 0;
+        if (n > kJointWood) {
+            __syncthreads();
+            continue;
+        }
         const double m = (M && r < R) ? (double)M[row * R + r] : 0.0;
-        double c[kJointK];
-#pragma unroll
-        for (int k = 0; k < kJointK; ++k) c[k] = 0.0;
-        double rhs = 0.0;
-        if (wood && rg.y - rg.x <= (uint32_t)kJointB) {
-            uint32_t cur_mid = 0;
-            const int n =
-                rg.y > rg.x ? joint_load_batch<T>(st, rg.x, rg.y, Fmid, Fleaf, R, cur_mid, V, Yb)
-                            : 0;
-            if (n <= kJointWood) {
-                joint_woodbury<T>(n, V, Yb, mu, m, Pinv, ws, R, row, out,
-                                  V + 16 * kJointRP, Lc);
-                continue;
-            }
-            joint_add_batch(n, c, rhs, V, Yb);
-        } else if (rg.y > rg.x) {
-            joint_accumulate<T, false>(st, rg.x, rg.y, Fmid, Fleaf, R, c, rhs, V, Yb);
-        }
-        if (M) rhs = fma(mu, m, rhs);
-        joint_solve_store<T>(c, rhs, p, row, R, out, flag, Lc, V);
-    }
-}
-
-// one segment of a heavy row: partial S (R x R, row-major) and rhs (R)
-template <typename T>
-__global__ __launch_bounds__(64) void k_joint_segments(const uint2 *__restrict__ st,
-                                                       const uint2 *__restrict__ seg,
-                                                       int64_t nseg, const T *__restrict__ Fmid,
-                                                       const T *__restrict__ Fleaf, int R,
-                                                       double *__restrict__ part) {
-    __shared__ double V[kJointB * kJointRP], Yb[kJointB];
-    const int h = threadIdx.x >> 5, r = threadIdx.x & 31;
-    for (int64_t q = blockIdx.x; q < nseg; q += gridDim.x) {
-        const uint2 sg = seg[q];
-        double c[kJointK];
-#pragma unroll
-        for (int k = 0; k < kJointK; ++k) c[k] = 0.0;
-        double rhs = 0.0;
-        joint_accumulate<T, true>(st, sg.x, sg.y, Fmid, Fleaf, R, c, rhs, V, Yb);
-        double *P = part + q * (int64_t)(R * R + R);
-        if (r < R) {
-#pragma unroll
-            for (int k = 0; k < kJointK; ++k)
-                if (2 * k + h < R) P[r * R + 2 * k + h] = c[k];
-            if (h == 0) P[R * R + r] = rhs;
-        }
-    }
-}
-
-// a heavy row: the sum of its segments' partials in segment order, solved
-template <typename T>
-__global__ __launch_bounds__(64) void k_joint_heavy(const uint4 *__restrict__ heavy,
-                                                    int64_t nheavy, int R,
-                                                    const double *__restrict__ part,
-                                                    const float *__restrict__ M,
-                                                    const double *__restrict__ H, double mu,
-                                                    double lam, T *__restrict__ out,
-                                                    int *__restrict__ flag) {
-    __shared__ double Tl[kJointRM * kJointRP], Lc[2 * 32];
-    const int h = threadIdx.x >> 5, r = threadIdx.x & 31;
-    double p[kJointK];
-    joint_shift(H, R, mu, lam, p);
-    for (int64_t hi = blockIdx.x; hi < nheavy; hi += gridDim.x) {
-        const uint4 hv = heavy[hi];  // (row, first segment, segments, 0)
-        double c[kJointK];
-#pragma unroll
-        for (int k = 0; k < kJointK; ++k) c[k] = 0.0;
-        double rhs = 0.0;
-        if (r < R) {
-            for (uint32_t q = hv.y; q < hv.y + hv.z; ++q) {
-                const double *P = part + (int64_t)q * (R * R + R);
-#pragma unroll
-                for (int k = 0; k < kJointK; ++k)
-                    if (2 * k + h < R) c[k] += P[r * R + 2 * k + h];
-                rhs += P[R * R + r];
-            }
-        }
-        if (M && r < R) rhs = fma(mu, (double)M[(int64_t)hv.x * R + r], rhs);
-        joint_solve_store<T>(c, rhs, p, (int64_t)hv.x, R, out, flag, Lc, Tl);
+        joint_woodbury<T>(n, V, Yb, mu, m, Pinv, ws, R, row, out, V + 16 * kJointRP, Bb);
     }
 }
 
@@ -1637,39 +1871,6 @@ __global__ __launch_bounds__(kBlock) void k_joint_f(const double *__restrict__ f
 // Accumulation is FP64; the next tile's rows are loaded before the current
 // tile's MFMAs.
 // ---------------------------------------------------------------------------
-// Raw 4-element runs (kept undecoded while in flight: half the registers of
-// doubles for FP32, a quarter for BF16).
-template <typename T>
-struct Run4;
-template <>
-struct Run4<float> {
-    float4 v;
-    __device__ __forceinline__ void load(const float *p) { v = *reinterpret_cast<const float4 *>(p); }
-    __device__ __forceinline__ void zero() { v = make_float4(0.f, 0.f, 0.f, 0.f); }
-    __device__ __forceinline__ double operator[](int i) const {
-        return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w;
-    }
-};
-template <>
-struct Run4<uint16_t> {
-    uint2 v;
-    __device__ __forceinline__ void load(const uint16_t *p) { v = *reinterpret_cast<const uint2 *>(p); }
-    __device__ __forceinline__ void zero() { v = make_uint2(0u, 0u); }
-    __device__ __forceinline__ double operator[](int i) const {
-        const uint32_t w = i < 2 ? v.x : v.y;
-        return __uint_as_float((i % 2 == 0) ? (w << 16) : (w & 0xFFFF0000u));
-    }
-};
-__device__ __forceinline__ void store4d(float *p, const double4v &a) {
-    *reinterpret_cast<float4 *>(p) = make_float4((float)a[0], (float)a[1], (float)a[2], (float)a[3]);
-}
-__device__ __forceinline__ void store4d(uint16_t *p, const double4v &a) {
-    uint2 w;
-    w.x = (uint32_t)f32_to_bf16((float)a[0]) | ((uint32_t)f32_to_bf16((float)a[1]) << 16);
-    w.y = (uint32_t)f32_to_bf16((float)a[2]) | ((uint32_t)f32_to_bf16((float)a[3]) << 16);
-    *reinterpret_cast<uint2 *>(p) = w;
-}
-
 // wa[c][t] = W[k(t)][16 c + column of MFMA row lane % 16]
 template <int NCT>
 __device__ __forceinline__ void load_rmat(const double *__restrict__ W, int lane,
@@ -2283,40 +2484,67 @@ int resident_blocks(K kernel, int block) {
     return n;
 }
 
-void launch_joint_rows(dfacto_ctx *ctx, const dfacto_tensor *Y, int m, int64_t nrows,
-                       const void *Fmid, const void *Fleaf, int R, const float *M,
-                       const double *H, double mu, double lam, const double *Pinv, double ws,
-                       const int *pflag, void *out, dfacto_dtype dtype, int *flag, double *part) {
-    if (nrows <= 0) return;
+size_t joint_part_doubles(int R, int64_t nseg) {
+    return (size_t)nseg * 16 * (R <= 16 ? JointSys<4>::kAll : JointSys<8>::kAll);
+}
+
+namespace {
+template <typename T, int NB, bool VEC>
+void joint_rows_t(dfacto_ctx *ctx, const dfacto_tensor *Y, int m, int64_t nrows, const T *F, int R,
+                  const float *M, const double *H, double mu, double lam, const double *Pinv,
+                  double ws, const int *pflag, T *out, int *flag, int *need, double *part) {
     hipStream_t s = ctx->stream;
-    const uint2 *st = Y->mode[m].stream;
+    // (an empty stream is never used, only read)
+    const uint2 *st = Y->mode[m].nentry > 0 ? Y->mode[m].stream : (const uint2 *)flag;
+    const bool by_mid = m == 1;
     // persistent: the grid is what the device holds at once, so no
     // workgroup waits for a second round
-    static const int occ_f32 = resident_blocks(k_joint_rows<float>, 64);
-    static const int occ_bf16 = resident_blocks(k_joint_rows<uint16_t>, 64);
-    const int occ = dtype == DFACTO_F32 ? occ_f32 : occ_bf16;
-    const unsigned grid =
-        (unsigned)std::min<int64_t>(nrows, (int64_t)std::max(1, ctx->num_cu) * occ);
+    static const int occ = resident_blocks(k_joint_rows<T, NB, VEC>, 64);
+    const unsigned grid = (unsigned)std::min<int64_t>((nrows + 3) / 4,
+                                                      (int64_t)std::max(1, ctx->num_cu) * occ);
     const int64_t nseg = Y->nseg[m], nheavy = Y->nheavy[m];
-    const unsigned gseg = (unsigned)std::max<int64_t>(1, std::min<int64_t>(nseg, 1 << 20));
-    const unsigned ghv = (unsigned)std::max<int64_t>(1, std::min<int64_t>(nheavy, 1 << 20));
-#define DF_JOINT(T)                                                                            \
-    hipLaunchKernelGGL(k_joint_rows<T>, dim3(grid), dim3(64), 0, s, st, Y->row_range[m], nrows, \
-                       (const T *)Fmid, (const T *)Fleaf, R, M, H, mu, lam, Pinv, ws, pflag,   \
-                       (T *)out, flag);                                                        \
-    if (nseg > 0) {                                                                            \
-        hipLaunchKernelGGL(k_joint_segments<T>, dim3(gseg), dim3(64), 0, s, st,               \
-                           Y->seg_range[m], nseg, (const T *)Fmid, (const T *)Fleaf, R, part); \
-        hipLaunchKernelGGL(k_joint_heavy<T>, dim3(ghv), dim3(64), 0, s, Y->heavy[m], nheavy,  \
-                           R, part, M, H, mu, lam, (T *)out, flag);                            \
+    hipLaunchKernelGGL((k_joint_rows<T, NB, VEC>), dim3(grid), dim3(64), 0, s, st, Y->row_range[m], nrows,
+                       F, by_mid, R, M, H, mu, lam, out, flag, need);
+    hipLaunchKernelGGL(k_joint_small<T>, dim3(grid), dim3(64), 0, s, st, Y->row_range[m], nrows, F,
+                       by_mid, R, M, mu, Pinv, ws, pflag, out, flag, need);
+    if (nseg > 0) {
+        const unsigned gseg = (unsigned)std::min<int64_t>(nseg, 1 << 20);
+        const unsigned ghv = (unsigned)std::min<int64_t>((nheavy + 3) / 4, 1 << 20);
+        hipLaunchKernelGGL((k_joint_segments<T, NB, VEC>), dim3(gseg), dim3(256), 0, s, st,
+                           Y->seg_range[m], nseg, F, by_mid, R, part);
+        hipLaunchKernelGGL((k_joint_heavy<T, NB>), dim3(ghv), dim3(64), 0, s, Y->heavy[m], nheavy, R,
+                           VEC, part, M, H, mu, lam, out, flag);
+    }
+    DF_LAUNCHED();
+}
+}  // namespace
+
+void launch_joint_rows(dfacto_ctx *ctx, const dfacto_tensor *Y, int m, int64_t nrows,
+                       const void *F, int R, const float *M, const double *H, double mu, double lam,
+                       const double *Pinv, double ws, const int *pflag, void *out,
+                       dfacto_dtype dtype, int *flag, int *need, double *part) {
+    if (nrows <= 0) return;
+    // rows of whole 4-element runs (R % 4 == 0) on their alignment are loaded
+    // and stored a run at a time, others by element
+    const size_t al = 4 * elem_size(dtype) - 1;
+    const bool vec = R % 4 == 0 && (((uintptr_t)F | (uintptr_t)out) & al) == 0;
+#define DF_JOINT_V(T, NB, V)                                                                   \
+    joint_rows_t<T, NB, V>(ctx, Y, m, nrows, (const T *)F, R, M, H, mu, lam, Pinv, ws, pflag,  \
+                           (T *)out, flag, need, part)
+#define DF_JOINT(T, NB)                        \
+    {                                          \
+        if (vec) DF_JOINT_V(T, NB, true);      \
+        else DF_JOINT_V(T, NB, false);         \
     }
     if (dtype == DFACTO_F32) {
-        DF_JOINT(float)
+        if (R <= 16) DF_JOINT(float, 4)
+        else DF_JOINT(float, 8)
     } else {
-        DF_JOINT(uint16_t)
+        if (R <= 16) DF_JOINT(uint16_t, 4)
+        else DF_JOINT(uint16_t, 8)
     }
+#undef DF_JOINT_V
 #undef DF_JOINT
-    DF_LAUNCHED();
 }
 
 void launch_joint_combine(dfacto_ctx *ctx, float *G, const void *F, const float *RY, double mu,

@@ -236,7 +236,7 @@ struct dfacto_tensor {
     // [x, y) of its entries in that mode's stream ((0, 0) for an empty row)
     bool ratings = false;
     uint2 *row_range[2] = {nullptr, nullptr};
-    // rows of more than kJointSeg entries, split into segments: seg_range[m]
+    // rows of more than kJointLight entries, in segments: seg_range[m]
     // (begin, end) per segment, heavy[m] (row, first segment, segments, 0)
     uint2 *seg_range[2] = {nullptr, nullptr};
     uint4 *heavy[2] = {nullptr, nullptr};
@@ -420,14 +420,18 @@ void launch_trial_factor(dfacto_ctx *ctx, const void *F, const float *G, double 
 void launch_sumsq3(dfacto_ctx *ctx, const float *const x[3], const int64_t n[3], double *part,
                    double *out);
 // joint matrix completion + tensor factorization pieces (dense.hip)
-constexpr int kJointSeg = 4096;  // entries per joint-ALS work item
-// Row m of the joint ALS for every row of ratings mode m: S = sum v^T v +
-// mu H + lam I.  Short rows use P^-1 = ws * Pinv (P = mu H + lam I; ws * I
-// when Pinv is null) when *pflag == 0, the others a Cholesky of S.
+constexpr int kJointLight = 256;   // most entries of a row solved without being split
+constexpr int kJointSeg = 2048;    // entries per segment of a longer row, and
+constexpr int kJointMaxSegs = 32;  // its most segments (longer ones then)
+// Row m of the joint ALS for every row of ratings mode m, F the other
+// factor: (sum v^T v + mu H + lam I) x = sum y v + mu M[row].  Short rows that
+// fail the pivot test use P^-1 = ws * Pinv (P = mu H + lam I; ws * I when Pinv
+// is null) when *pflag == 0.  part: joint_part_doubles(R, Y->nseg[m]) doubles.
+size_t joint_part_doubles(int R, int64_t nseg);
 void launch_joint_rows(dfacto_ctx *ctx, const dfacto_tensor *Y, int m, int64_t nrows,
-                       const void *Fmid, const void *Fleaf, int R, const float *M,
-                       const double *H, double mu, double lam, const double *Pinv, double ws,
-                       const int *pflag, void *out, dfacto_dtype dtype, int *flag, double *part);
+                       const void *F, int R, const float *M, const double *H, double mu, double lam,
+                       const double *Pinv, double ws, const int *pflag, void *out,
+                       dfacto_dtype dtype, int *flag, int *need, double *part);
 void launch_joint_combine(dfacto_ctx *ctx, float *G, const void *F, const float *RY, double mu,
                           double lam, int64_t n, dfacto_dtype dtype);
 // fit = 1 - sqrt(max(0, ||X||^2 + lambda^T (GA*GB*GC) lambda - 2 <C diag(lambda), M>)) / ||X||
