@@ -630,10 +630,13 @@ dfacto_status dfacto_gd_step(dfacto_ctx *ctx, const dfacto_tensor *t, int R, dfa
         const size_t es = elem_size(dtype);
         size_t off[4], o = 0;
         for (int m = 0; m < 3; ++m) off[m] = o, o += ((size_t)n[m] * es + 255) & ~(size_t)255;
-        off[3] = o, o += (size_t)n[0] * 4;
+        off[3] = o, o += ((size_t)n[0] * 4 + 255) & ~(size_t)255;
+        const size_t ogram = o;  // the Grams' partial sums
+        o += sizeof(double) * trial_gram_doubles(R);
         char *wt = (char *)ws_get(ctx, dfacto_ctx::kTrial, o);
         void *T[3] = {wt + off[0], wt + off[1], wt + off[2]};
         float *M = (float *)(wt + off[3]);
+        double *gpart = (double *)(wt + ogram);
         double host[2];
         DF_HIP(hipMemcpyAsync(host, d_gn2, 2 * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
         DF_HIP(hipStreamSynchronize(ctx->stream));
@@ -644,11 +647,10 @@ dfacto_status dfacto_gd_step(dfacto_ctx *ctx, const dfacto_tensor *t, int R, dfa
         const ModeData &md = t->mode[0];
         double alpha = ls->alpha0;
         for (int trial = 0; trial < ls->max_trials; ++trial) {
-            for (int m = 0; m < 3; ++m) launch_trial_factor(ctx, d_F[m], d_G[m], alpha, T[m], dtype, n[m]);
+            launch_trial_factors(ctx, d_F, d_G, alpha, T, dtype, n);
             // f at the trial point, as in dfacto_gd_grad: Grams, the mode-0
             // MTTKRP, <T_0, M> by the gradient-row pass, then the combination
-            for (int m = 0; m < 3; ++m) launch_gram(ctx, T[m], dtype, t->dims[m], R, sw.GT[m]);
-            launch_hadamard(ctx, R, sw.GT[1], sw.GT[2], reg, sw.HT);
+            launch_trial_grams(ctx, T, dtype, t->dims, R, sw.GT, reg, sw.HT, gpart);
             launch_mttkrp(ctx, t, 0, R, dtype, T[md.leaf], T[md.mid], M);
             launch_gd_rows(ctx, M, T[0], dtype, t->dims[0], R, sw.HT, sw.part_t);
             launch_gd_f(ctx, R, sw.GT[0], sw.GT[1], sw.GT[2], sw.part_t,
