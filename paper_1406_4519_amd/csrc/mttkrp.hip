@@ -816,20 +816,27 @@ __global__ __launch_bounds__(kBlock) MTTKRP_OCCUPANCY void k_mttkrp(
 //     the mid row in LDS;
 //   stage 2: a group adds P * mid row over the fibers of whole output rows.
 // Every fiber's and every row's sum runs in stream order, so the result is
-// bitwise that of mttkrp_group_chunk.
+// bitwise that of mttkrp_group_chunk.  What bounds it is the chain of round
+// trips of a block (about a third each of the time in front of the stages, in
+// stage 1 and in stage 2) times the rounds of blocks, so blocks are kept small:
+// LDS for the R columns there are (R = 10: 32 KB, five blocks a CU, not 47 KB
+// and three), and stage 1 takes ten entries at once by selects (59 registers;
+// sixteen with branches 100).  1M nonzeros, R = 10, a mode: 53 -> 43 us; either
+// change alone 51.
 constexpr int kBlkEntries = 640;  // a chunk of chunk_len <= 512: one more segment at most
 constexpr int kBlkFibers = kBlkEntries / 2;
 static_assert(kBlkEntries >= DFACTO_CHUNK_DEFAULT + kFiberCap, "a chunk fits the block's LDS");
 
 template <typename T, int CPL, int G>
-__global__ __launch_bounds__(kBlock) void k_mttkrp_block(
+__global__ __launch_bounds__(kBlock, 5) void k_mttkrp_block(
     const uint2 *__restrict__ st_, const uint32_t *__restrict__ cstart,
     const T *__restrict__ Fleaf, const T *__restrict__ Fmid, int R, float *__restrict__ out_,
-    float *__restrict__ carry_) {
-    constexpr int W = CPL * G, NG = kBlock / G, U = 16;
+    float *__restrict__ carry_, int ld) {
+    constexpr int W = CPL * G, NG = kBlock / G, U = 10;
     constexpr int kWords = kBlkEntries / 64, kFWords = kBlkFibers / 64;
     __shared__ uint2 ent[kBlkEntries];
-    __shared__ alignas(16) float Ps[kBlkFibers * W], Ms[kBlkFibers * W];
+    extern __shared__ float Ps[];  // P, then the mid rows: ld floats a segment
+    float *Ms = Ps + kBlkFibers * ld;
     __shared__ uint32_t frow[kBlkFibers];               // the row of each segment's header
     __shared__ uint64_t hmask[kWords], rmask[kFWords];  // headers; segments that open a row
     __shared__ int before[kWords + 1];                  // headers before each word of hmask
@@ -849,7 +856,8 @@ __global__ __launch_bounds__(kBlock) void k_mttkrp_block(
     __syncthreads();
     if (tid <= kWords) {
         int n = 0;
-        for (int w = 0; w < tid; ++w) n += __popcll(hmask[w]);
+#pragma unroll
+        for (int w = 0; w < kWords; ++w) n += w < tid ? __popcll(hmask[w]) : 0;
         before[tid] = n;
     }
     // the first header from entry b on (L: none), and the headers before b
@@ -868,6 +876,13 @@ __global__ __launch_bounds__(kBlock) void k_mttkrp_block(
     const int beg = next_head(g * share), end = next_head((g + 1) * share);
     __syncthreads();
     const int nf = before[kWords], f0 = heads_before(g * share);
+    for (int i = tid; i < L; i += kBlock) {
+        const uint2 w = ent[i];
+        if ((int32_t)w.x >= 0) continue;
+        const int f = heads_before(i);
+        frow[f] = w.y;
+        if (w.x & kRootBit) atomicOr((uint32_t *)rmask + (f >> 5), 1u << (f & 31));
+    }
 
     // stage 1
     const int c0 = blockIdx.y * W + lane * CPL;
@@ -875,8 +890,8 @@ __global__ __launch_bounds__(kBlock) void k_mttkrp_block(
     const uint32_t rowb = (uint32_t)R * (uint32_t)sizeof(T);
     const uint64_t leaf0 = (uint64_t)(uintptr_t)Fleaf + colb, mid0 = (uint64_t)(uintptr_t)Fmid + colb;
     {
-        float *ps = Ps + (f0 - 1) * W + lane * CPL, *ms = Ms + (f0 - 1) * W + lane * CPL;
-        int f = f0 - 1;
+        const bool mine = lane * CPL < ld;
+        int pos = (f0 - 1) * ld + lane * CPL;
         float p[CPL];
 #pragma unroll
         for (int q = 0; q < CPL; ++q) p[q] = 0.f;
@@ -891,31 +906,26 @@ __global__ __launch_bounds__(kBlock) void k_mttkrp_block(
                     (const DF_GLOBAL T *)(uintptr_t)(((int32_t)w[u].x < 0 ? mid0 : leaf0) +
                                                      (uint64_t)(w[u].x & kIdxMask) * rowb),
                     r[u]);
+            // Headers and nonzeros by selects: a wave's groups stand at both.
+            // A header stores its mid row, a nonzero the P up to it (its
+            // fiber's last one stays).  A header leaves P = 0, or NaN for an
+            // Inf or NaN in the mid row, as the lane groups have it for all
+            // but a chunk's first segment.
             static_for<0, U>([&](auto uc) {
                 constexpr int u = decltype(uc)::value;
-                if (at + u >= end) return;
-                if ((int32_t)w[u].x < 0) {
-                    if (f >= f0) store_lds<CPL>(ps, p);
-                    ++f;
-                    ps += W;
-                    ms += W;
-                    store_lds<CPL>(ms, r[u]);
-                    if (lane == 0) {
-                        frow[f] = w[u].y;
-                        if (w[u].x & kRootBit) atomicOr((uint32_t *)rmask + (f >> 5), 1u << (f & 31));
-                    }
-                    // 0, or NaN for an Inf or NaN in the mid row, as the lane
-                    // groups have it for all but a chunk's first segment
+                const bool h = (int32_t)w[u].x < 0;
+                const float y = h ? 0.f : __uint_as_float(w[u].y);
+                float v[CPL];
 #pragma unroll
-                    for (int q = 0; q < CPL; ++q) p[q] = f ? fmaf(0.f, r[u][q], 0.f) : 0.f;
-                } else {
-#pragma unroll
-                    for (int q = 0; q < CPL; ++q)
-                        p[q] = fmaf(__uint_as_float(w[u].y), r[u][q], p[q]);
+                for (int q = 0; q < CPL; ++q) {
+                    p[q] = fmaf(y, r[u][q], h ? 0.f : p[q]);
+                    if (u == 0 && at == 0) p[q] = 0.f;
+                    v[q] = h ? r[u][q] : p[q];
                 }
+                pos += h ? ld : 0;
+                if (at + u < end && mine) store_lds<CPL>(Ps + pos + (h ? kBlkFibers * ld : 0), v);
             });
         }
-        if (f >= f0) store_lds<CPL>(ps, p);
     }
     __syncthreads();
 
@@ -938,9 +948,10 @@ __global__ __launch_bounds__(kBlock) void k_mttkrp_block(
         float acc[CPL];
 #pragma unroll
         for (int q = 0; q < CPL; ++q) acc[q] = 0.f;
-        const float *ps = Ps + f * W + lane * CPL, *ms = Ms + f * W + lane * CPL;
+        const int at = f * ld + min(lane * CPL, ld - CPL);
+        const float *ps = Ps + at, *ms = Ms + at;
 #pragma unroll 4
-        for (; f < e; ++f, ps += W, ms += W) {
+        for (; f < e; ++f, ps += ld, ms += ld) {
             float p[CPL], m[CPL];
             load_lds<CPL>(ps, p);
             load_lds<CPL>(ms, m);
@@ -1438,10 +1449,12 @@ bool launch_block(dfacto_ctx *ctx, const ModeData &md, int R, dfacto_dtype dtype
     if ((uint64_t)md.nchunk * slices > (uint64_t)(narrow ? 20 : 16) * ctx->num_cu) return false;
     auto go = [&](auto tc, auto cplc, auto gc) {
         using T = typename decltype(tc)::type;
-        hipLaunchKernelGGL((k_mttkrp_block<T, decltype(cplc)::value, decltype(gc)::value>),
-                           dim3((unsigned)md.nchunk, slices), dim3(kBlock), 0, ctx->stream,
-                           md.stream, md.chunk_start, (const T *)tb.leaf, (const T *)tb.mid, R,
-                           out, carry);
+        constexpr int CPL = decltype(cplc)::value, W = CPL * decltype(gc)::value;
+        const int ld = (std::min(R, W) + CPL - 1) / CPL * CPL;
+        hipLaunchKernelGGL((k_mttkrp_block<T, CPL, decltype(gc)::value>),
+                           dim3((unsigned)md.nchunk, slices), dim3(kBlock),
+                           sizeof(float) * 2 * kBlkFibers * (size_t)ld, ctx->stream, md.stream,
+                           md.chunk_start, (const T *)tb.leaf, (const T *)tb.mid, R, out, carry, ld);
     };
     auto by_type = [&](auto tc) {
         if (narrow) go(tc, IntC<1>{}, IntC<8>{});
