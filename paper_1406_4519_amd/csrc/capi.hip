@@ -508,13 +508,21 @@ dfacto_status dfacto_als_iter(dfacto_ctx *ctx, const dfacto_tensor *t, int R, df
         // mode n's MTTKRP and is joined before mode n's lambda step.  Mode 0's
         // solve follows the Grams of F[1] and F[2], also formed there.  The
         // MTTKRP is enqueued before the side stream's part.
+        // Tensors of at most a chunk per compute unit, R <= 16: the solve lasts
+        // no longer than the six event operations of a mode cost the host, and
+        // runs on the main stream.  us an iteration, beside / in line: 20K
+        // nonzeros R = 8 198 / 125, R = 16 194 / 141; 60K 201 / 155, 193 / 175;
+        // 400K R = 8 200 / 196, R = 16 200 / 232; 60K R = 20 213 / 249.
+        int64_t nchunk = 0;
+        for (int m = 0; m < 3; ++m) nchunk = std::max<int64_t>(nchunk, t->mode[m].nchunk);
+        const bool beside = R > 16 || nchunk > ctx->num_cu;
         for (int n = 0; n < 3; ++n) {
             const ModeData &md = t->mode[n];
-            DF_HIP(hipEventRecord(ctx->ev_fork, ctx->stream));
+            if (beside) DF_HIP(hipEventRecord(ctx->ev_fork, ctx->stream));
             launch_mttkrp(ctx, t, n, R, dtype, d_F[md.leaf], d_F[md.mid], M);
-            DF_HIP(hipStreamWaitEvent(ctx->side, ctx->ev_fork, 0));
+            if (beside) DF_HIP(hipStreamWaitEvent(ctx->side, ctx->ev_fork, 0));
             {
-                OnStream on(ctx, ctx->side);
+                OnStream on(ctx, beside ? ctx->side : ctx->stream);
                 if (n == 0) {
                     launch_gram(ctx, d_F[1], dtype, t->dims[1], R, sw.G[1]);
                     launch_gram(ctx, d_F[2], dtype, t->dims[2], R, sw.G[2]);
@@ -525,9 +533,9 @@ dfacto_status dfacto_als_iter(dfacto_ctx *ctx, const dfacto_tensor *t, int R, df
                 launch_solve(ctx, R, sw.G[(n + 1) % 3], sw.G[(n + 2) % 3], reg, sw.Hinv,
                              sw.solve_scratch, sw.flag + n);
             }
-            DF_HIP(hipEventRecord(ctx->ev_join, ctx->side));
+            if (beside) DF_HIP(hipEventRecord(ctx->ev_join, ctx->side));
             launch_gram(ctx, M, DFACTO_F32, t->dims[n], R, sw.MtM);
-            DF_HIP(hipStreamWaitEvent(ctx->stream, ctx->ev_join, 0));
+            if (beside) DF_HIP(hipStreamWaitEvent(ctx->stream, ctx->ev_join, 0));
             // writes G[n] (the new factor's Gram) and W; reads H^-1
             launch_als_lambda(ctx, R, n, sw.Hinv, sw.MtM, sw.G[n], sw.W, d_lambda, sw.G[0],
                               sw.G[1], t->normsq, d_fit, sw.lam_scratch);
