@@ -814,7 +814,10 @@ dfacto_status dfacto_joint_als_iter(dfacto_ctx *ctx, const dfacto_tensor *X,
         const int64_t nseg = std::max(Y->nseg[0], Y->nseg[1]);
         double *part = (double *)ws_get(ctx, dfacto_ctx::kJoint,
                                         sizeof(double) * (joint_part_doubles(R, nseg) + 1));
-        DF_HIP(hipMemsetAsync(sw.flag, 0, 4 * sizeof(int), ctx->stream));
+        // flag words: [0] a row failed, [1] and [2] the solves' pseudo-inverse marks,
+        // [3 + n] mode n has short rows left to k_joint_small (a word a mode: what
+        // the users' rows need says nothing of the items')
+        DF_HIP(hipMemsetAsync(sw.flag, 0, 5 * sizeof(int), ctx->stream));
         ensure_side(ctx);
         for (int n = 0; n < 3; ++n) {
             const int p = (n + 1) % 3, q = (n + 2) % 3;
@@ -849,7 +852,7 @@ dfacto_status dfacto_joint_als_iter(dfacto_ctx *ctx, const dfacto_tensor *X,
                 const double ws = mu > 0.0 ? 1.0 / mu : 1.0 / lam;
                 launch_joint_rows(ctx, Y, n, X->dims[n], d_F[1 - n], R, mu > 0.0 ? M : nullptr,
                                   sw.H[n], mu, lam, Pinv, ws, sw.flag + 2, d_F[n], dtype, sw.flag,
-                                  sw.flag + 3, part);
+                                  sw.flag + 3 + n, part);
             } else if (mu > 0.0) {
                 launch_rowmap(ctx, M, X->dims[2], R, sw.Hinv, d_F[2], dtype);
             } else {
