@@ -1751,14 +1751,18 @@ __device__ int joint_load_batch(const uint2 *__restrict__ st, uint32_t b, uint32
 
 // A row of at most kJointWood entries (vectors v_e in rows of V, ratings in
 // Yb) solved without factorizing its own S = P + V^T V, from P^-1 (the same
-// for every row of the mode) by the Sherman-Morrison-Woodbury identity:
-//   b = sum_e y_e v_e + mu m,  z = P^-1 b,  u_e = P^-1 v_e,
-//   K = I + [v_e . u_f],  t = [v_e . z],  K w = t,  x = z - sum_e w_e u_e.
+// for every row of the mode).  With b = sum_e y_e v_e + mu m the
+// Sherman-Morrison-Woodbury identity and S^-1 V^T = P^-1 V^T K^-1 give
+//   z = P^-1 mu m,  u_e = P^-1 v_e,  K = I + [v_e . u_f],
+//   t = [y_e - v_e . z],  K w = t,  x = z + sum_e w_e u_e.
+// The ratings enter behind K^-1: with them in z, x would be the difference of
+// two terms of size P^-1 V^T y, far above x where P is small beside V^T V,
+// which is when a row comes here.
 // P^-1 = ws * Pinv (R x R, row-major), or ws * I when Pinv is null.  K is
 // symmetric positive definite with eigenvalues >= 1 and is solved by
 // Gauss-Jordan without pivoting, lane (e, f) = e * 8 + f holding K[e][f]
 // and lane (e, n) holding t[e].  U (kJointRM rows of kJointRP doubles, apart
-// from V's first n rows) holds u_e and z; Bb (32 doubles) carries b.
+// from V's first n rows) holds u_e and z; Bb (32 doubles) carries mu m.
 template <typename T>
 __device__ void joint_woodbury(int n, const double *V, const double *Yb, double mu, double m,
                                const double *__restrict__ Pinv, double ws, int R, int64_t row,
@@ -1770,10 +1774,7 @@ __device__ void joint_woodbury(int n, const double *V, const double *Yb, double 
         const int q = 2 * k + h;
         wr[k] = (r < R && q < R) ? (Pinv ? ws * Pinv[r * R + q] : (q == r ? ws : 0.0)) : 0.0;
     }
-    double b = 0.0;
-    for (int e = 0; e < n; ++e) b = fma(Yb[e], V[e * kJointRP + r], b);
-    b = fma(mu, m, b);
-    if (h == 0) Bb[r] = b;
+    if (h == 0) Bb[r] = mu * m;
     __syncthreads();
     double zp = 0.0;
 #pragma unroll
@@ -1795,10 +1796,10 @@ __device__ void joint_woodbury(int n, const double *V, const double *Yb, double 
 #pragma unroll 4
         for (int q = 0; q < kJointRM; ++q) g = fma(U[ge * kJointRP + q], V[gf * kJointRP + q], g);
     }
-    const double tv = __shfl(g, n * 8 + ge, 64);  // t[ge] = z . v_ge
+    const double tv = __shfl(g, n * 8 + ge, 64);  // v_ge . z
     double a = 0.0;
     if (ge < n && gf < n) a = g + (ge == gf ? 1.0 : 0.0);
-    if (ge < n && gf == n) a = tv;
+    if (ge < n && gf == n) a = Yb[ge] - tv;
     for (int j = 0; j < n; ++j) {
         const double inv = 1.0 / lane_bcast(a, j * 9);  // K's pivot at step j
         const double rowj = __shfl(a, j * 8 + gf, 64);
@@ -1806,7 +1807,7 @@ __device__ void joint_woodbury(int n, const double *V, const double *Yb, double 
         a = ge == j ? rowj * inv : fma(-colj * inv, rowj, a);
     }
     double x = z;
-    for (int e = 0; e < n; ++e) x = fma(-lane_bcast(a, e * 8 + n), U[e * kJointRP + r], x);
+    for (int e = 0; e < n; ++e) x = fma(lane_bcast(a, e * 8 + n), U[e * kJointRP + r], x);
     if (h == 0 && r < R) st_out<T>(out, row * R + r, x);
     __syncthreads();  // U, V and Bb are free again
 }

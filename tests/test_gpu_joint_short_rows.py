@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_util import build, to_host64, DEV
+from gpu_util import build, say, to_host64, DEV
 from paper_1406_4519_amd import dfacto, gen
 
 pytestmark = pytest.mark.gpu
@@ -80,5 +80,53 @@ def test_short_row_without_a_valid_inverse_is_a_failure(ctx):
     with pytest.raises(dfacto.DfactoError) as err:
         dfacto.joint_als_iter(ctx, X, Y, [torch.from_numpy(f).to(DEV) for f in F], 1.0, lam)
     assert err.value.status == dfacto.E_NUMERIC
+    X.close()
+    Y.close()
+
+
+@pytest.mark.parametrize("mu", [0.0, 1.0])
+@pytest.mark.parametrize("R", [6, 16, 32])
+def test_short_rows_have_the_ridge_solution(ctx, R, mu):
+    """Rows of fewer than min(8, R) ratings with P of about 1e-17 (mu = 0: lam I;
+    mu = 1: word factors of 1e-10): S = P + V^T V fails the test, and x is
+    z0 + P^-1 V^T K^-1 (y - V z0), z0 = mu P^-1 M[row], K = I + V P^-1 V^T
+    (S^-1 V^T = P^-1 V^T K^-1), nothing of which is ill-conditioned."""
+    I, J, K, lam = 151, 211, 20, 1e-17
+    rng = np.random.default_rng(5)
+    n = [r % 8 if r % 8 < R else 0 for r in range(I)]
+    yi = np.repeat(np.arange(I), n)
+    yj = np.arange(len(yi)) % J  # no item more than 3 times
+    yv = rng.integers(1, 6, len(yi)).astype(np.float64)
+    Y = _ratings(ctx, (I, J), yi, yj, yv)
+    coo = gen.uniform_distinct((I, J, K), 6000, seed=72)
+    coo.val *= np.float32(1e-7)
+    X = build(ctx, coo)
+    F = [rng.uniform(0, 1, (d, R)).astype(np.float32) for d in (I, J, K)]
+    F[2] *= np.float32(1e-10)
+    Fd = [torch.from_numpy(f).to(DEV) for f in F]
+    dfacto.joint_als_iter(ctx, X, Y, Fd, mu, lam)
+    torch.cuda.synchronize()
+    new, C, worst = [to_host64(f) for f in Fd], F[2].astype(np.float64), 0.0
+    seen = [torch.from_numpy(f).to(DEV) for f in F]
+    for m, own, oth in ((0, yi, yj), (1, yj, yi)):
+        O = to_host64(seen[1 - m])
+        P = mu * ((O.T @ O) * (C.T @ C)) + lam * np.eye(R)
+        M = to_host64(dfacto.mttkrp(ctx, X, m, seen))
+        for r in range(len(new[m])):
+            e = np.flatnonzero(own == r)
+            V = O[oth[e]]
+            z0, U = np.linalg.solve(P, mu * M[r]), np.linalg.solve(P, V.T).T
+            Kr = np.eye(len(e)) + V @ U.T
+            d = U.T @ np.linalg.solve(Kr, yv[e] - V @ z0) if len(e) else np.zeros(R)
+            x = z0 + d
+            # stored in FP32; P^-1, K and their products in FP64
+            cond = np.linalg.cond(P) * (np.linalg.cond(Kr) if len(e) else 1.0)
+            tol = 1.01 * 2.0 ** -24 * np.linalg.norm(x) + \
+                64 * R * EPS * cond * (np.linalg.norm(z0) + np.linalg.norm(d))
+            err = np.linalg.norm(new[m][r] - x)
+            assert err <= tol, (m, r, len(e), err, tol)
+            worst = max(worst, err / max(tol, 1e-300))
+        seen[m] = Fd[m]
+    say(f"  joint short rows R={R} mu={mu}: worst error / bound {worst:.3f}")
     X.close()
     Y.close()
