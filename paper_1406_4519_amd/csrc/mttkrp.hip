@@ -604,14 +604,17 @@ __device__ __forceinline__ uint64_t spread_groups(uint64_t b) {
 // at four columns per lane keep two batches of eight (one batch is gathered
 // while the other is added up: R = 32, 50M nonzeros 2112 -> 2058 us; 16 in one
 // batch spill, 3170); narrower ones one batch of 16 (R = 16: 1885 us against
-// 1965 at 8, 2008 at 24, and 3028 with two batches).
+// 1965 at 8, 2008 at 24, and 3028 with two batches).  BF16 rows at four columns
+// over two or four lanes, which only a tuned group tries, hold more entries a
+// lane and take eight.
 template <typename T, int CPL, int G, int NCH>
 constexpr int batch_entries() {
     if (G == 64) return CPL * NCH == 1 ? 32 : (CPL * NCH == 2 ? 16 : 8);
-    return CPL <= 2 || (CPL == 4 && sizeof(T) == 2) ? 16 : 8;
+    return CPL <= 2 || (CPL == 4 && sizeof(T) == 2 && G >= 8) ? 16 : 8;
 }
 
-template <typename T, int CPL, int G, int NCH>
+// TWO: FP32 rows at four columns per lane in two batches (else in one)
+template <typename T, int CPL, int G, int NCH, bool TWO>
 __device__ __forceinline__ void mttkrp_group_chunk(const uint2 *__restrict__ st_,
                                                    const uint32_t *__restrict__ cstart,
                                                    uint32_t nchunk, const T *__restrict__ Fleaf,
@@ -754,7 +757,7 @@ __device__ __forceinline__ void mttkrp_group_chunk(const uint2 *__restrict__ st_
     };
     uint2 wn[KL];
     fetch(cs + 1, wn);
-    if constexpr (WAVE || (CPL == 4 && sizeof(T) == 4)) {
+    if constexpr (WAVE || (TWO && CPL == 4 && sizeof(T) == 4)) {
         // Each batch's entries are requested before the rows of the batch
         // ahead of it, so that waiting for them leaves those rows in flight.
         if (nmax > 0) {
@@ -799,9 +802,9 @@ __global__ __launch_bounds__(kBlock) MTTKRP_OCCUPANCY void k_mttkrp(
     const uint2 *__restrict__ st, const uint32_t *__restrict__ cstart, uint32_t nchunk,
     const T *__restrict__ Fleaf, const T *__restrict__ Fmid, int R, float *__restrict__ out,
     float *__restrict__ carry) {
-    mttkrp_group_chunk<T, CPL, G, NCH>(st, cstart, nchunk, Fleaf, Fmid, R, out, carry,
-                                       (blockIdx.x * (uint32_t)kBlock + threadIdx.x) / G,
-                                       threadIdx.x % G);
+    mttkrp_group_chunk<T, CPL, G, NCH, true>(st, cstart, nchunk, Fleaf, Fmid, R, out, carry,
+                                             (blockIdx.x * (uint32_t)kBlock + threadIdx.x) / G,
+                                             threadIdx.x % G);
 }
 
 // ---- one block per chunk ---------------------------------------------------
@@ -980,7 +983,11 @@ __global__ __launch_bounds__(kBlock) void k_mttkrp_res(
 // consecutive chunks) in a fixed order, item blockIdx.x, blockIdx.x +
 // gridDim.x, ...; each lane group takes kper consecutive chunks of its item
 // in turn.  Every chunk writes its own rows and carry, so the grid, the
-// shape and kper change no result.
+// shape and kper change no result.  One batch in flight for every form: a
+// second one does not fit beside the member's fields and the loops (FP32 at
+// four columns then spilled 9 to 64 registers; an iteration of eight tensors of
+// 2M nonzeros, R = 48 2206 us with it, 2186 without, R = 64 3098 and 3086,
+// R = 32 1188 and 1187).
 template <typename T, int CPL, int G, int NCH>
 __global__ __launch_bounds__(kBlock) MTTKRP_OCCUPANCY void k_mttkrp_group(
     const GroupMttkrp *__restrict__ desc, const uint2 *__restrict__ items, uint32_t nitems,
@@ -991,9 +998,9 @@ __global__ __launch_bounds__(kBlock) MTTKRP_OCCUPANCY void k_mttkrp_group(
         const uint2 w = items[it];
         const GroupMttkrp &d = desc[w.x];
         for (uint32_t q = 0; q < kper; ++q)
-            mttkrp_group_chunk<T, CPL, G, NCH>(d.stream, d.chunk_start, d.nchunk,
-                                               (const T *)d.Fleaf, (const T *)d.Fmid, d.R, d.out,
-                                               d.carry, w.y + first + q, lane);
+            mttkrp_group_chunk<T, CPL, G, NCH, false>(d.stream, d.chunk_start, d.nchunk,
+                                                      (const T *)d.Fleaf, (const T *)d.Fmid, d.R,
+                                                      d.out, d.carry, w.y + first + q, lane);
     }
 }
 
@@ -1424,6 +1431,18 @@ void with_shape(dfacto_dtype dtype, const MttkrpShape &sh, F &&f) {
     else by_cpl(TypeC<uint16_t>{});
 }
 
+// The forms that rows of a type are walked in: eight columns per lane only for
+// BF16 (mttkrp_shape); the main kernel's rows take at least five lanes, or
+// single columns (main_shape).
+template <typename T, int CPL>
+constexpr bool form_ok() {
+    return CPL < 8 || sizeof(T) == 2;
+}
+template <typename T, int CPL, int G>
+constexpr bool main_form_ok() {
+    return form_ok<T, CPL>() && (CPL == 1 || G >= 8);
+}
+
 // The tables the main kernel gathers from, their row stride (the kernel's
 // column count), and for padded tables the padded output rows the kernel
 // writes (rows_out of them), copied back to R columns after the fix-ups.
@@ -1529,10 +1548,14 @@ void run(dfacto_ctx *ctx, const ModeData &md, int R, dfacto_dtype dtype, const M
                 using T = typename decltype(tc)::type;
                 constexpr int CPL = decltype(cplc)::value, G = decltype(gc)::value,
                               NCH = decltype(nchc)::value;
-                const unsigned blocks = (nchunk + kBlock / G - 1) / (kBlock / G);
-                hipLaunchKernelGGL((k_mttkrp<T, CPL, G, NCH>), dim3(blocks), dim3(kBlock), 0, s,
-                                   md.stream, md.chunk_start, nchunk, (const T *)tb.leaf,
-                                   (const T *)tb.mid, R, out, carry);
+                if constexpr (main_form_ok<T, CPL, G>()) {
+                    const unsigned blocks = (nchunk + kBlock / G - 1) / (kBlock / G);
+                    hipLaunchKernelGGL((k_mttkrp<T, CPL, G, NCH>), dim3(blocks), dim3(kBlock), 0,
+                                       s, md.stream, md.chunk_start, nchunk, (const T *)tb.leaf,
+                                       (const T *)tb.mid, R, out, carry);
+                } else {
+                    throw Error{DFACTO_E_UNSUPPORTED, "no MTTKRP kernel for this form"};
+                }
             });
         prof_mark(ctx);
     }
@@ -1909,10 +1932,14 @@ void launch_mttkrp_group(dfacto_ctx *ctx, dfacto_dtype dtype, const MttkrpShape 
     if (kper < 1 || grid < 1) throw Error{DFACTO_E_INVALID, "grouped MTTKRP launch shape"};
     with_shape(dtype, sh, [&](auto tc, auto cplc, auto gc, auto nchc) {
         using T = typename decltype(tc)::type;
-        hipLaunchKernelGGL((k_mttkrp_group<T, decltype(cplc)::value, decltype(gc)::value,
-                                           decltype(nchc)::value>),
-                           dim3(grid), dim3(kBlock), 0, ctx->stream, d_desc, d_items, nitems,
-                           kper);
+        constexpr int CPL = decltype(cplc)::value;
+        if constexpr (form_ok<T, CPL>())
+            hipLaunchKernelGGL((k_mttkrp_group<T, CPL, decltype(gc)::value,
+                                               decltype(nchc)::value>),
+                               dim3(grid), dim3(kBlock), 0, ctx->stream, d_desc, d_items, nitems,
+                               kper);
+        else
+            throw Error{DFACTO_E_UNSUPPORTED, "no grouped MTTKRP kernel for this form"};
     });
     DF_LAUNCHED();
 }
