@@ -538,7 +538,9 @@ dfacto_status dfacto_joint_als_iter(dfacto_ctx *ctx, const dfacto_tensor *X,
  * d_F: in/out factors (layout and alignment as dfacto_gd_grad); d_G: the
  * gradients at the input point (out); ls: host struct; info: host struct,
  * filled on return.  The trial factors live in a context workspace
- * (sum of the factor sizes plus one dims[0] x R FP32 buffer).  Synchronizes
+ * (sum of the factor sizes plus one dims[0] x R FP32 buffer, or for R <= 64
+ * the partial sums of the smallest factor's Gram where those are larger: an
+ * R x R FP64 block for every 128 or more of its rows).  Synchronizes
  * the stream once per trial (the test needs f on the host).  Errors: as
  * dfacto_gd_grad, plus DFACTO_E_INVALID for a NULL ls or info, alpha0 <= 0
  * or not finite, shrink or c outside (0, 1), max_trials outside [1, 1000]. */

@@ -638,13 +638,21 @@ dfacto_status dfacto_gd_step(dfacto_ctx *ctx, const dfacto_tensor *t, int R, dfa
         const size_t es = elem_size(dtype);
         size_t off[4], o = 0;
         for (int m = 0; m < 3; ++m) off[m] = o, o += ((size_t)n[m] * es + 255) & ~(size_t)255;
-        off[3] = o, o += ((size_t)n[0] * 4 + 255) & ~(size_t)255;
-        const size_t ogram = o;  // the Grams' partial sums
-        o += sizeof(double) * trial_gram_doubles(R);
+        // The Grams' partial sums: the two larger ones where single Grams keep
+        // theirs (both streams' buffers, idle here), the smallest in the
+        // MTTKRP's output, which is written after them.
+        size_t gd[3];
+        for (int m = 0; m < 3; ++m) gd[m] = trial_gram_doubles(t->dims[m], R);
+        const int least = (int)(std::min_element(gd, gd + 3) - gd);
+        off[3] = o, o += std::max((size_t)n[0] * 4, gd[least] * sizeof(double));
         char *wt = (char *)ws_get(ctx, dfacto_ctx::kTrial, o);
         void *T[3] = {wt + off[0], wt + off[1], wt + off[2]};
         float *M = (float *)(wt + off[3]);
-        double *gpart = (double *)(wt + ogram);
+        const size_t pb = sizeof(double) * 256 * (size_t)R * R;  // as ws_prepare has them
+        double *gpart[3];
+        gpart[least] = (double *)M;
+        gpart[(least + 1) % 3] = (double *)ws_get(ctx, dfacto_ctx::kPartial, pb);
+        gpart[(least + 2) % 3] = (double *)ws_get(ctx, dfacto_ctx::kPartialSide, pb);
         double host[2];
         DF_HIP(hipMemcpyAsync(host, d_gn2, 2 * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
         DF_HIP(hipStreamSynchronize(ctx->stream));

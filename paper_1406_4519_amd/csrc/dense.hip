@@ -2512,13 +2512,14 @@ void launch_trial_factors(dfacto_ctx *ctx, void *const F[3], float *const G[3], 
     DF_LAUNCHED();
 }
 
-size_t trial_gram_doubles(int R) {
-    return R <= 16 * kMfmaMaxTiles ? (size_t)3 * 256 * R * R : 0;
+size_t trial_gram_doubles(int64_t rows, int R) {
+    if (R > 16 * kMfmaMaxTiles) return 0;  // one Gram at a time, in launch_gram's own buffer
+    return (size_t)gram_plan(rows, R, nullptr, DFACTO_F32).nblk * R * R;
 }
 
 void launch_trial_grams(dfacto_ctx *ctx, void *const F[3], dfacto_dtype dtype,
                         const int64_t rows[3], int R, double *const G[3], double reg, double *H,
-                        double *part) {
+                        double *const part[3]) {
     if (R > 16 * kMfmaMaxTiles) {
         for (int m = 0; m < 3; ++m) launch_gram(ctx, F[m], dtype, rows[m], R, G[m]);
         launch_hadamard(ctx, R, G[1], G[2], reg, H);
@@ -2530,7 +2531,7 @@ void launch_trial_grams(dfacto_ctx *ctx, void *const F[3], dfacto_dtype dtype,
     int nt = 1;
     for (int m = 0; m < 3; ++m) {
         const GramPlan gp = gram_plan(rows[m], R, F[m], dtype);
-        jobs.j[m] = GramJob{F[m], rows[m], R, (uint32_t)gp.nblk, part + (size_t)m * 256 * R * R, G[m]};
+        jobs.j[m] = GramJob{F[m], rows[m], R, (uint32_t)gp.nblk, part[m], G[m]};
         nblk = std::max(nblk, (unsigned)gp.nblk);
         vec = vec && gp.vec;
         nt = gp.nt;

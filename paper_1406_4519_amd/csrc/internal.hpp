@@ -417,11 +417,11 @@ int gd_rows_partials(int64_t rows, int R, const float *G, const void *F, dfacto_
 constexpr int kSumsqBlocks = 256;
 void launch_trial_factors(dfacto_ctx *ctx, void *const F[3], float *const G[3], double alpha,
                           void *const out[3], dfacto_dtype dtype, const int64_t n[3]);
-// the three Grams and H = G[1] * G[2] + reg I (part: trial_gram_doubles(R))
-size_t trial_gram_doubles(int R);
+// the three Grams and H = G[1] * G[2] + reg I (part[m]: trial_gram_doubles(rows[m], R))
+size_t trial_gram_doubles(int64_t rows, int R);
 void launch_trial_grams(dfacto_ctx *ctx, void *const F[3], dfacto_dtype dtype,
                         const int64_t rows[3], int R, double *const G[3], double reg, double *H,
-                        double *part);
+                        double *const part[3]);
 void launch_sumsq3(dfacto_ctx *ctx, const float *const x[3], const int64_t n[3], double *part,
                    double *out);
 // joint matrix completion + tensor factorization pieces (dense.hip)
