@@ -1303,12 +1303,16 @@ void build_row_ranges(dfacto_ctx *ctx, dfacto_tensor *t) {
             const uint32_t len = std::max<uint32_t>(
                 kJointSeg, (e - b + kJointMaxSegs - 1) / kJointMaxSegs);
             const uint32_t first = (uint32_t)seg[m].size(), n = (e - b + len - 1) / len;
+            if (t->batch[m].empty() || first + n - t->batch[m].back().second > kJointBatch)
+                t->batch[m].push_back({(int64_t)heavy[m].size(), (int64_t)first});
+            t->batch_segs = std::max<int64_t>(t->batch_segs, first + n - t->batch[m].back().second);
             heavy[m].push_back(make_uint4((uint32_t)r, first, n, 0u));
             for (uint32_t x = 0; x < n; ++x)
                 seg[m].push_back(make_uint2(b + x * len, x + 1 < n ? b + (x + 1) * len : e));
         }
         t->nseg[m] = (int64_t)seg[m].size();
         t->nheavy[m] = (int64_t)heavy[m].size();
+        t->batch[m].push_back({t->nheavy[m], t->nseg[m]});
         t->seg_range[m] = tensor_alloc<uint2>(t, t->nseg[m]);
         t->heavy[m] = tensor_alloc<uint4>(t, t->nheavy[m]);
         if (t->nseg[m] > 0) {

@@ -818,10 +818,9 @@ dfacto_status dfacto_joint_als_iter(dfacto_ctx *ctx, const dfacto_tensor *X,
         }
         Small sw = small_ws(ctx, R);
         float *M = (float *)ws_get(ctx, dfacto_ctx::kM, sizeof(float) * (size_t)max_dim(X) * R);
-        // the heavy rows' partial systems
-        const int64_t nseg = std::max(Y->nseg[0], Y->nseg[1]);
+        // the heavy rows' partial systems, a batch of rows at a time
         double *part = (double *)ws_get(ctx, dfacto_ctx::kJoint,
-                                        sizeof(double) * (joint_part_doubles(R, nseg) + 1));
+                                        sizeof(double) * (joint_part_doubles(R, Y->batch_segs) + 1));
         // flag words: [0] a row failed, [1] and [2] the solves' pseudo-inverse marks,
         // [3 + n] mode n has short rows left to k_joint_small (a word a mode: what
         // the users' rows need says nothing of the items')

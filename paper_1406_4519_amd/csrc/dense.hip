@@ -1668,10 +1668,10 @@ __global__ __launch_bounds__(256, 3) void k_joint_segments(
 }
 
 // heavy rows, four a wave: the sum of a row's partial systems in segment
-// order, solved
+// order (part begins with segment seg0's), solved
 template <typename T, int NB>
 __global__ __launch_bounds__(64, 2) void k_joint_heavy(const uint4 *__restrict__ heavy,
-                                                    int64_t nheavy, int R, bool vec,
+                                                    int64_t nheavy, int64_t seg0, int R, bool vec,
                                                     const double *__restrict__ part,
                                                     const float *__restrict__ M,
                                                     const double *__restrict__ H, double mu,
@@ -1690,7 +1690,7 @@ __global__ __launch_bounds__(64, 2) void k_joint_heavy(const uint4 *__restrict__
         joint_start<NB>(S, P, l);
         joint_rhs<NB>(S, M, row, R, mu, mine, l);
         for (uint32_t q = hv.y; q < hv.y + hv.z; ++q) {
-            const double *pt = part + (int64_t)q * (Sys::kAll * 16) + 4 * i + j;
+            const double *pt = part + ((int64_t)q - seg0) * (Sys::kAll * 16) + 4 * i + j;
             double v[Sys::kAll];  // all loads in flight
 #pragma unroll
             for (int x = 0; x < Sys::kAll; ++x) v[x] = pt[x * 16];
@@ -2595,18 +2595,19 @@ void joint_rows_t(dfacto_ctx *ctx, const dfacto_tensor *Y, int m, int64_t nrows,
     static const int occ = resident_blocks(k_joint_rows<T, NB, VEC>, 64);
     const unsigned grid = (unsigned)std::min<int64_t>((nrows + 3) / 4,
                                                       (int64_t)std::max(1, ctx->num_cu) * occ);
-    const int64_t nseg = Y->nseg[m], nheavy = Y->nheavy[m];
     hipLaunchKernelGGL((k_joint_rows<T, NB, VEC>), dim3(grid), dim3(64), 0, s, st, Y->row_range[m], nrows,
                        F, by_mid, R, M, H, mu, lam, out, flag, need);
     hipLaunchKernelGGL(k_joint_small<T>, dim3(grid), dim3(64), 0, s, st, Y->row_range[m], nrows, F,
                        by_mid, R, M, mu, Pinv, ws, pflag, out, flag, need);
-    if (nseg > 0) {
-        const unsigned gseg = (unsigned)std::min<int64_t>(nseg, 1 << 20);
-        const unsigned ghv = (unsigned)std::min<int64_t>((nheavy + 3) / 4, 1 << 20);
-        hipLaunchKernelGGL((k_joint_segments<T, NB, VEC>), dim3(gseg), dim3(256), 0, s, st,
-                           Y->seg_range[m], nseg, F, by_mid, R, part);
-        hipLaunchKernelGGL((k_joint_heavy<T, NB>), dim3(ghv), dim3(64), 0, s, Y->heavy[m], nheavy, R,
-                           VEC, part, M, H, mu, lam, out, flag);
+    const auto &cut = Y->batch[m];
+    for (size_t q = 0; q + 1 < cut.size(); ++q) {
+        const auto [row0, seg0] = cut[q];
+        const int64_t rows = cut[q + 1].first - row0, segs = cut[q + 1].second - seg0;
+        hipLaunchKernelGGL((k_joint_segments<T, NB, VEC>), dim3((unsigned)segs), dim3(256), 0, s,
+                           st, Y->seg_range[m] + seg0, segs, F, by_mid, R, part);
+        hipLaunchKernelGGL((k_joint_heavy<T, NB>), dim3((unsigned)((rows + 3) / 4)), dim3(64), 0,
+                           s, Y->heavy[m] + row0, rows, seg0, R, VEC, part, M, H, mu, lam, out,
+                           flag);
     }
     DF_LAUNCHED();
 }

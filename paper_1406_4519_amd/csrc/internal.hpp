@@ -6,6 +6,7 @@
 #include <cstdint>
 #include <cstdio>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "dfacto.h"
@@ -241,6 +242,10 @@ struct dfacto_tensor {
     uint2 *seg_range[2] = {nullptr, nullptr};
     uint4 *heavy[2] = {nullptr, nullptr};
     int64_t nseg[2] = {0, 0}, nheavy[2] = {0, 0};
+    // the heavy rows in batches of at most kJointBatch segments: (first row,
+    // first segment) of each, then the ends
+    std::vector<std::pair<int64_t, int64_t>> batch[2];
+    int64_t batch_segs = 0;  // most segments of a batch
 };
 
 struct dfacto_ctx {
@@ -428,10 +433,15 @@ void launch_sumsq3(dfacto_ctx *ctx, const float *const x[3], const int64_t n[3],
 constexpr int kJointLight = 256;   // most entries of a row solved without being split
 constexpr int kJointSeg = 2048;    // entries per segment of a longer row, and
 constexpr int kJointMaxSegs = 32;  // its most segments (longer ones then)
+// Segments whose partial systems (R > 16: 5.6 KB each) are held at once: ten
+// rounds of the device's blocks, 46 MB.  Without a limit rows of a few hundred
+// ratings would take 22 bytes per rating.
+constexpr int64_t kJointBatch = 8192;
+static_assert(kJointBatch >= kJointMaxSegs, "a row's segments are in one batch");
 // Row m of the joint ALS for every row of ratings mode m, F the other
 // factor: (sum v^T v + mu H + lam I) x = sum y v + mu M[row].  Short rows that
 // fail the pivot test use P^-1 = ws * Pinv (P = mu H + lam I; ws * I when Pinv
-// is null) when *pflag == 0.  part: joint_part_doubles(R, Y->nseg[m]) doubles.
+// is null) when *pflag == 0.  part: joint_part_doubles(R, Y->batch_segs) doubles.
 size_t joint_part_doubles(int R, int64_t nseg);
 void launch_joint_rows(dfacto_ctx *ctx, const dfacto_tensor *Y, int m, int64_t nrows,
                        const void *F, int R, const float *M, const double *H, double mu, double lam,
