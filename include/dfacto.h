@@ -582,11 +582,14 @@ dfacto_status dfacto_profile_read(dfacto_ctx *ctx, int64_t *launches, double *ms
 
 /* Measurement of the MTTKRP's memory-request ceiling (Section 3.2: the
  * product is a scan of the mode's flattening with one factor-row gather per
- * stored nonzero and per fiber).  Runs the main MTTKRP kernel's memory
- * requests for `mode` -- the same work chunks, lane groups, batches and row
- * loads -- with the arithmetic replaced by a plain sum of each gathered row.
- * pattern 0: each entry gathers its own row (the MTTKRP's exact request
- * sequence); 1: a row drawn uniformly at random from the same factor (leaf
+ * stored nonzero and per fiber).  Runs the loads of the main MTTKRP kernel's
+ * lane-group form for `mode` -- the kernel's own code: the same work chunks,
+ * tables, lane groups, batches and row loads -- with the arithmetic replaced
+ * by a plain sum of each gathered row and without the stores of output rows.
+ * (dfacto_mttkrp takes its one-block-per-chunk form where the chunks are too
+ * few to fill the device; the probe does not.)
+ * pattern 0: each entry gathers its own row (the MTTKRP's exact sequence of
+ * loads); 1: a row drawn uniformly at random from the same factor (leaf
  * factor for a nonzero, mid factor for a header); 2: a row among that
  * factor's first 4096; 3: no gathers, the flattening is only read; 4: a row
  * among the factor's first 32; 5: a row of a 128-row table held in LDS

@@ -613,15 +613,23 @@ constexpr int batch_entries() {
     return CPL <= 2 || (CPL == 4 && sizeof(T) == 2 && G >= 8) ? 16 : 8;
 }
 
+// No probe: the product itself.  A probe (below) walks the same chunk with the
+// same requests for stream entries and rows, only adds up what it loads, and
+// may replace the address that an entry gathers from.
+struct NoProbe {
+    static constexpr int kPat = -1;
+};
+
 // TWO: FP32 rows at four columns per lane in two batches (else in one)
-template <typename T, int CPL, int G, int NCH, bool TWO>
+template <typename T, int CPL, int G, int NCH, bool TWO, class Probe = NoProbe>
 __device__ __forceinline__ void mttkrp_group_chunk(const uint2 *__restrict__ st_,
                                                    const uint32_t *__restrict__ cstart,
                                                    uint32_t nchunk, const T *__restrict__ Fleaf,
                                                    const T *__restrict__ Fmid, int R,
                                                    float *__restrict__ out_,
                                                    float *__restrict__ carry_, uint32_t gid,
-                                                   int lane) {
+                                                   int lane, const Probe &probe = Probe{}) {
+    constexpr int PAT = Probe::kPat;
     constexpr bool WAVE = G == 64;
     constexpr int U = batch_entries<T, CPL, G, NCH>();
     constexpr int KL = (U + G - 1) / G;  // entries held per lane
@@ -680,11 +688,13 @@ __device__ __forceinline__ void mttkrp_group_chunk(const uint2 *__restrict__ st_
     for (int c = 0; c < NCH; ++c) {
 #pragma unroll
         for (int q = 0; q < CPL; ++q) acc[c][q] = p[c][q] = 0.f;
+        if constexpr (PAT > 0) continue;
         RowLoad<T, CPL>::load(
             (const DF_GLOBAL T *)((const DF_GLOBAL char *)gptr(Fmid) + colb[c] +
                                   (uint64_t)(live ? h0.x & kIdxMask : 0u) * rowb),
             mrow[c]);
-        dst[c] = ((h0.x & kRootBit) ? out + (size_t)h0.y * R : carry + (size_t)gc * R) + col[c];
+        if constexpr (PAT < 0)
+            dst[c] = ((h0.x & kRootBit) ? out + (size_t)h0.y * R : carry + (size_t)gc * R) + col[c];
     }
 
     struct Batch {
@@ -708,8 +718,12 @@ __device__ __forceinline__ void mttkrp_group_chunk(const uint2 *__restrict__ st_
         for (int k = 0; k < KL; ++k) {
             const bool v = at + (uint32_t)lane + G * k < last;
             const bool h = (int32_t)wl[k].x < 0;
-            const uint64_t a = (uint64_t)(uintptr_t)(h ? Fmid : Fleaf) +
-                               (uint64_t)(wl[k].x & kIdxMask) * rowb;
+            uint64_t a;
+            if constexpr (PAT <= 0)
+                a = (uint64_t)(uintptr_t)(h ? Fmid : Fleaf) + (uint64_t)(wl[k].x & kIdxMask) * rowb;
+            else
+                a = probe.place(wl[k].x, at + (uint32_t)lane + G * k, (uint64_t)(uintptr_t)Fleaf,
+                                (uint64_t)(uintptr_t)Fmid, rowb);
             lo[k] = (uint32_t)a;
             hi[k] = (uint32_t)(a >> 32);
             b.hdr[k] = __ballot(v && h);
@@ -719,12 +733,22 @@ __device__ __forceinline__ void mttkrp_group_chunk(const uint2 *__restrict__ st_
         }
         static_for<0, U>([&](auto uc) {
             constexpr int u = decltype(uc)::value;
-            const uint32_t l = bcast(lo[u / G], uc), h = bcast(hi[u / G], uc);
-            const DF_GLOBAL char *a =
-                (const DF_GLOBAL char *)(uintptr_t)(((uint64_t)h << 32) | l);
+            if constexpr (PAT == 3) {  // nothing gathered: the entries alone
+                const float y = __uint_as_float(bcast(b.y[u / G], uc) & 0x3F7FFFFFu);
 #pragma unroll
-            for (int c = 0; c < NCH; ++c)
-                RowLoad<T, CPL>::load((const DF_GLOBAL T *)(a + colb[c]), b.g[u][c]);
+                for (int q = 0; q < CPL; ++q) b.g[u][0][q] = y;
+            } else {
+                const uint32_t l = bcast(lo[u / G], uc), h = bcast(hi[u / G], uc);
+                if constexpr (PAT >= 5) {
+                    probe.load(l, h, colb[0], b.g[u][0]);
+                } else {
+                    const DF_GLOBAL char *a =
+                        (const DF_GLOBAL char *)(uintptr_t)(((uint64_t)h << 32) | l);
+#pragma unroll
+                    for (int c = 0; c < NCH; ++c)
+                        RowLoad<T, CPL>::load((const DF_GLOBAL T *)(a + colb[c]), b.g[u][c]);
+                }
+            }
         });
     };
     auto add = [&](const Batch &b, auto fullc) {
@@ -732,6 +756,13 @@ __device__ __forceinline__ void mttkrp_group_chunk(const uint2 *__restrict__ st_
             constexpr int u = decltype(uc)::value;
             constexpr int k = u / G, sh = u % G;
             constexpr bool full = decltype(fullc)::value;
+            if constexpr (PAT >= 0) {
+                const bool have = full || __builtin_amdgcn_inverse_ballot_w64(spread_groups<G>(
+                                              ((b.nz[k] | b.hdr[k]) >> sh) & kFirst));
+#pragma unroll
+                for (int q = 0; q < CPL; ++q) acc[0][q] += have ? b.g[u][0][q] : 0.f;
+                return;
+            }
             const uint32_t y = bcast(b.y[k], uc);
             const uint64_t hm = spread_groups<G>((b.hdr[k] >> sh) & kFirst);
             const uint64_t nm = full ? ~hm : spread_groups<G>((b.nz[k] >> sh) & kFirst);
@@ -788,6 +819,13 @@ __device__ __forceinline__ void mttkrp_group_chunk(const uint2 *__restrict__ st_
             fetch(cs + 1 + i + U, wn);
             add(b, std::false_type{});
         }
+    }
+    if constexpr (PAT >= 0) {  // a sum per lane (of the first mid row too), so nothing is elided
+        float sum = 0.f;
+#pragma unroll
+        for (int q = 0; q < CPL; ++q) sum += PAT == 0 ? acc[0][q] + mrow[0][q] : acc[0][q];
+        if (gid < nchunk) out[(size_t)gid * G + lane] = sum;
+        return;
     }
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
@@ -1005,16 +1043,23 @@ __global__ __launch_bounds__(kBlock) MTTKRP_OCCUPANCY void k_mttkrp_group(
 }
 
 // ---- gather ceiling --------------------------------------------------------
-// The main kernel's memory requests without its arithmetic: the same work
-// chunks, lane groups, batches of kUnroll entries (shared through
-// ds_swizzle) and row loads, but every gathered row is only summed.  PAT
-// selects the row that an entry gathers:
+// The main kernel's memory requests without its arithmetic and its stores of
+// rows: mttkrp_group_chunk itself, with the same work chunks, lane groups,
+// batches, address sharing and row loads, but every gathered row is only
+// summed.  PAT selects the row that an entry gathers:
 //   0  the entry's own row (leaf for a nonzero, mid for a header): the
-//      MTTKRP's exact request sequence;
+//      MTTKRP's exact sequence of loads;
 //   1  a row drawn uniformly from the same table (hash of the position);
 //   2  a row among the table's first 4096 (a working set that stays in L2);
-//   3  none: the stream is read, nothing is gathered.
-// Each lane writes its sum to sink[gid * G + lane], so nothing is elided.
+//   3  none: the stream is read, nothing is gathered;
+//   4  a row among the table's first 32;
+//   5  a row of a 128-row table in LDS;
+//   6-9 leaf rows (a header's mid index modulo the leaf rows) by buffer loads:
+//      6 every offset out of range, 7 the entry's own row, 8 half of the
+//      entries (a hash bit) from the LDS table and half own rows, split by a
+//      branch, 9 the same half split without a branch (an out-of-range buffer
+//      load beside an LDS load).
+// Each lane writes its sum to sink[chunk * G + lane].
 __device__ __forceinline__ uint32_t probe_hash(uint32_t x) {
     x ^= x >> 16;
     x *= 0x7feb352dU;
@@ -1025,36 +1070,68 @@ __device__ __forceinline__ uint32_t probe_hash(uint32_t x) {
 }
 
 constexpr int kProbeLdsRows = 128, kProbeLdsRowElems = 64;
+constexpr uint32_t kProbeOut = 0xFFFFFF00u;  // past the end of every probed table
 
-template <typename T, int CPL, int G, bool SMALL, int PAT>
+template <typename T, int CPL, int PAT>
+struct GatherProbe {
+    static constexpr int kPat = PAT;
+    uint32_t nleaf, nmid;
+    const T *lds;  // kProbeLdsRows rows of kProbeLdsRowElems (5, 8, 9)
+    __amdgpu_buffer_rsrc_t rsrc;  // the leaf table (6 to 9)
+    // what the lane that holds entry `x` at stream position `e` shares: an
+    // address (1, 2, 4), an LDS offset (5), the leaf row's offset and, above it,
+    // the LDS offset with the top bit for the LDS half (8, 9)
+    __device__ __forceinline__ uint64_t place(uint32_t x, uint32_t e, uint64_t leaf, uint64_t mid,
+                                              uint32_t rowb) const {
+        const bool hdr = (int32_t)x < 0;
+        const uint32_t h = probe_hash(e);
+        constexpr uint32_t ldsb = kProbeLdsRowElems * (uint32_t)sizeof(T);
+        if constexpr (PAT == 1 || PAT == 2 || PAT == 4) {
+            const uint32_t n = hdr ? nmid : nleaf, lim = PAT == 2 ? 4096u : 32u;
+            const uint32_t idx = PAT == 1 ? (uint32_t)(((uint64_t)h * n) >> 32)
+                                          : (h & (lim - 1)) % (n < lim ? n : lim);
+            return (hdr ? mid : leaf) + (uint64_t)idx * rowb;
+        } else if constexpr (PAT == 5) {
+            return (h & (kProbeLdsRows - 1)) * ldsb;
+        } else if constexpr (PAT >= 7) {
+            const uint32_t own = ((x & kIdxMask) % nleaf) * rowb;
+            if constexpr (PAT == 7) return own;
+            return ((uint64_t)((h >> 25) * ldsb | (h << 31)) << 32) | own;
+        } else {
+            return 0;
+        }
+    }
+    __device__ __forceinline__ void load(uint32_t lo, uint32_t hi, uint32_t colb,
+                                         float (&v)[CPL]) const {
+        auto from_lds = [&](uint32_t off, float (&o)[CPL]) {
+            RowLoad<T, CPL>::load((const T *)((const char *)lds + off + colb), o);
+        };
+        if constexpr (PAT == 5) {
+            from_lds(lo, v);
+        } else if constexpr (PAT == 6) {
+            BufLoad<T, CPL>::load(rsrc, kProbeOut, v);
+        } else if constexpr (PAT == 7) {
+            BufLoad<T, CPL>::load(rsrc, lo + colb, v);
+        } else if constexpr (PAT == 8) {
+            if (hi >> 31) from_lds(hi & 0x7FFFFFFFu, v);
+            else BufLoad<T, CPL>::load(rsrc, lo + colb, v);
+        } else {
+            float gv[CPL], lv[CPL];
+            BufLoad<T, CPL>::load(rsrc, hi >> 31 ? kProbeOut : lo + colb, gv);
+            from_lds(hi >> 31 ? hi & 0x7FFFFFFFu : 0u, lv);
+#pragma unroll
+            for (int q = 0; q < CPL; ++q) v[q] = hi >> 31 ? lv[q] : gv[q];
+        }
+    }
+};
+
+template <typename T, int CPL, int G, int PAT>
 __global__ __launch_bounds__(kBlock) MTTKRP_OCCUPANCY void k_gather_probe(
     const uint2 *__restrict__ st, const uint32_t *__restrict__ cstart, uint32_t nchunk,
     const T *__restrict__ Fleaf, const T *__restrict__ Fmid, int R, uint32_t nleaf,
     uint32_t nmid, float *__restrict__ sink) {
-    const uint32_t gid0 = (blockIdx.x * (uint32_t)kBlock + threadIdx.x) / G;
-    const int lane = threadIdx.x % G;
-    // groups past the last chunk walk an empty range (they still take part
-    // in the block's barrier)
-    const uint32_t gid = gid0 < nchunk ? gid0 : nchunk;
-    const uint32_t cs = cstart[gid], ce = gid0 < nchunk ? cstart[gid + 1] : cs;
-    const int col = lane * CPL;
-    const bool act = col < R;
-    const T *leafb = Fleaf + (act ? col : 0), *midb = Fmid + (act ? col : 0);
-    auto row_off = [&](uint32_t idx) -> size_t {
-        if constexpr (SMALL) return (size_t)(uint32_t)__umul24(idx, (uint32_t)R);
-        else return (size_t)idx * (size_t)R;
-    };
-    float acc[CPL];
-#pragma unroll
-    for (int q = 0; q < CPL; ++q) acc[q] = 0.f;
-    // PAT 5, 8, 9: rows read from an LDS table (kProbeLdsRows rows)
     constexpr bool kLds = PAT == 5 || PAT == 8 || PAT == 9;
-    __shared__ T lds_rows[kLds ? kProbeLdsRows * kProbeLdsRowElems : 1];
-    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)Fleaf, (short)0, (int)((uint64_t)nleaf * R * sizeof(T) < 0xFFFFFF00ull
-                                            ? (uint64_t)nleaf * R * sizeof(T)
-                                            : 0xFFFFFF00ull),
-        0x00020000);
+    __shared__ alignas(16) T lds_rows[kLds ? kProbeLdsRows * kProbeLdsRowElems : 1];
     if constexpr (kLds) {
         const uint64_t have = (uint64_t)nleaf * (uint64_t)R;
         const uint32_t nfill = have < (uint64_t)kProbeLdsRowElems ? (uint32_t)have
@@ -1063,93 +1140,17 @@ __global__ __launch_bounds__(kBlock) MTTKRP_OCCUPANCY void k_gather_probe(
             lds_rows[x] = Fleaf[(uint32_t)x % nfill];
         __syncthreads();
     }
-    constexpr bool kShare = G <= 32;
-    constexpr int KL = kShare ? (kUnroll + G - 1) / G : kUnroll;
-    auto load_batch = [&](uint32_t at, uint2 (&wl)[KL]) {
-#pragma unroll
-        for (int k = 0; k < KL; ++k)
-            wl[k] = kShare ? load_entry(st + at + lane + G * k) : load_entry(st + at + k);
-    };
-    auto expand = [&](const uint2 (&wl)[KL], uint2 (&w)[kUnroll]) {
-        static_for<0, kUnroll>([&](auto uc) {
-            constexpr int u = decltype(uc)::value;
-            if constexpr (kShare) {
-                constexpr int pat = (0x1F & ~(G - 1)) | ((u % G) << 5);
-                w[u].x = (uint32_t)__builtin_amdgcn_ds_swizzle((int)wl[u / G].x, pat);
-                w[u].y = (uint32_t)__builtin_amdgcn_ds_swizzle((int)wl[u / G].y, pat);
-            } else {
-                w[u] = wl[u];
-            }
-        });
-    };
-    uint2 wn[KL];
-    load_batch(cs, wn);
-    for (uint32_t e = cs; e < ce; e += kUnroll) {
-        uint2 w[kUnroll];
-        expand(wn, w);
-        load_batch(e + kUnroll, wn);
-        float g[kUnroll][CPL];
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            const bool hdr = (int32_t)w[u].x < 0;
-            if constexpr (PAT == 3) {
-#pragma unroll
-                for (int q = 0; q < CPL; ++q) g[u][q] = __uint_as_float(w[u].y & 0x3F7FFFFFu);
-            } else if constexpr (PAT == 5) {
-                const uint32_t h = probe_hash(e + u) & (kProbeLdsRows - 1);
-                RowLoad<T, CPL>::load(lds_rows + h * (kProbeLdsRowElems) + (act ? col : 0), g[u]);
-            } else if constexpr (PAT >= 6) {
-                // buffer loads of leaf rows: 6 every offset out of range; 7 the
-                // entry's own row (mid index taken modulo the leaf rows); 8 half
-                // of the entries (a hash bit) from the LDS table, the other
-                // half own rows, split by a branch; 9 the same half split
-                // without a branch (out-of-range buffer load + LDS row 0)
-                const uint32_t idx = (w[u].x & kIdxMask) % nleaf;
-                const uint32_t boff = (uint32_t)(idx * (uint32_t)R + (act ? col : 0)) * sizeof(T);
-                const bool lhot = (probe_hash(e + u) & 1u) != 0;
-                const uint32_t h = probe_hash(e + u) >> 25;  // < 128 rows
-                if constexpr (PAT == 6) {
-                    BufLoad<T, CPL>::load(rsrc, 0xFFFFFF00u, g[u]);
-                } else if constexpr (PAT == 7) {
-                    BufLoad<T, CPL>::load(rsrc, boff, g[u]);
-                } else if constexpr (PAT == 8) {
-                    if (lhot)
-                        RowLoad<T, CPL>::load(lds_rows + h * kProbeLdsRowElems + (act ? col : 0),
-                                              g[u]);
-                    else
-                        BufLoad<T, CPL>::load(rsrc, boff, g[u]);
-                } else {
-                    float gv[CPL], lv[CPL];
-                    BufLoad<T, CPL>::load(rsrc, lhot ? 0xFFFFFF00u : boff, gv);
-                    RowLoad<T, CPL>::load(lds_rows + (lhot ? h : 0u) * kProbeLdsRowElems +
-                                              (act ? col : 0),
-                                          lv);
-#pragma unroll
-                    for (int q = 0; q < CPL; ++q) g[u][q] = lhot ? lv[q] : gv[q];
-                }
-            } else {
-                uint32_t idx;
-                if constexpr (PAT == 0) {
-                    idx = w[u].x & kIdxMask;
-                } else {
-                    const uint32_t n = hdr ? nmid : nleaf;
-                    const uint32_t h = probe_hash(e + u);
-                    const uint32_t lim = PAT == 2 ? 4096u : 32u;
-                    idx = PAT == 1 ? (uint32_t)(((uint64_t)h * n) >> 32)
-                                   : (h & (lim - 1)) % (n < lim ? n : lim);
-                }
-                RowLoad<T, CPL>::load((hdr ? midb : leafb) + row_off(idx), g[u]);
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u)
-#pragma unroll
-            for (int q = 0; q < CPL; ++q) acc[q] += (e + u < ce) ? g[u][q] : 0.f;
-    }
-    float s = 0.f;
-#pragma unroll
-    for (int q = 0; q < CPL; ++q) s += acc[q];
-    if (gid0 < nchunk) sink[(size_t)gid * G + lane] = s;
+    GatherProbe<T, CPL, PAT> probe;
+    probe.nleaf = nleaf;
+    probe.nmid = nmid;
+    probe.lds = lds_rows;
+    const uint64_t bytes = (uint64_t)nleaf * R * sizeof(T);
+    probe.rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)Fleaf, (short)0, (int)(bytes < kProbeOut ? bytes : kProbeOut), 0x00020000);
+    // (8 and 9, two loads an entry, have no registers for a second batch)
+    mttkrp_group_chunk<T, CPL, G, 1, (PAT < 8)>(st, cstart, nchunk, Fleaf, Fmid, R, sink, sink,
+                                                (blockIdx.x * (uint32_t)kBlock + threadIdx.x) / G,
+                                                threadIdx.x % G, probe);
 }
 
 // ---- fix-up: carries of split rows, and empty rows ------------------------
@@ -1867,50 +1868,51 @@ void launch_gather_probe(dfacto_ctx *ctx, const dfacto_tensor *t, int mode, int 
                          dfacto_dtype dtype, const void *Fleaf, const void *Fmid, int pattern,
                          float *sink) {
     const ModeData &md = t->mode[mode];
-    const MttkrpShape sh =
-        main_shape(mttkrp_shape(R, dtype, Fleaf, Fmid, sink, md.perm_leaf != nullptr), R, dtype,
-                   md.nchunk, ctx->num_cu);
-    if (sh.nch != 1) throw Error{DFACTO_E_UNSUPPORTED, "the gather probe takes R <= 64 * CPL"};
-    if ((pattern == 5 || pattern >= 8) && R > kProbeLdsRowElems)
+    // the tables, row stride and lane groups that launch_mttkrp's call would
+    // have with an output aligned as the sink
+    auto shape = [&](int cols, const void *leaf, const void *mid) {
+        const MttkrpShape sh = mttkrp_shape(cols, dtype, leaf, mid, sink, md.perm_leaf != nullptr);
+        return main_shape(sh, cols, dtype, md.nchunk, ctx->num_cu);
+    };
+    const int S = kernel_cols(t, R, dtype);
+    if (shape(S, Fleaf, Fmid).nch != 1)
+        throw Error{DFACTO_E_UNSUPPORTED, "the gather probe takes R <= 64 * CPL"};
+    if ((pattern == 5 || pattern >= 8) && S > kProbeLdsRowElems)
         throw Error{DFACTO_E_UNSUPPORTED, "the LDS patterns take R <= 64"};
-    if (pattern >= 6 && (uint64_t)t->dims[md.leaf] * R * elem_size(dtype) >= 0xFFFFFF00ull)
+    if (pattern >= 6 && (uint64_t)t->dims[md.leaf] * S * elem_size(dtype) >= kProbeOut)
         throw Error{DFACTO_E_UNSUPPORTED, "the buffer patterns take a leaf table below 4 GB"};
-    const bool sm = mttkrp_small(t, mode);
     const uint32_t nchunk = (uint32_t)md.nchunk;
     if (nchunk == 0) return;
     const uint32_t nleaf = (uint32_t)t->dims[md.leaf], nmid = (uint32_t)t->dims[md.mid];
-    const Tables tb = gather_tables(ctx, t, mode, R, dtype, Fleaf, Fmid);
-    Fleaf = tb.leaf;
-    Fmid = tb.mid;
+    const Tables tb = gather_tables(ctx, t, mode, R, dtype, Fleaf, Fmid, nullptr, 0);
+    const MttkrpShape sh =
+        tb.pad_out ? shape(tb.stride, tb.leaf, tb.mid) : shape(R, Fleaf, Fmid);
     with_shape(dtype, sh, [&](auto tc, auto cplc, auto gc, auto) {
         using T = typename decltype(tc)::type;
         constexpr int CPL = decltype(cplc)::value, G = decltype(gc)::value;
-        if constexpr (G <= 64) {
+        if constexpr (main_form_ok<T, CPL, G>()) {
             const unsigned blocks = (nchunk + kBlock / G - 1) / (kBlock / G);
             auto go = [&](auto kern) {
                 prof_mark(ctx);
                 hipLaunchKernelGGL(kern, dim3(blocks), dim3(kBlock), 0, ctx->stream, md.stream,
-                                   md.chunk_start, nchunk, (const T *)Fleaf, (const T *)Fmid, R,
-                                   nleaf, nmid, sink);
+                                   md.chunk_start, nchunk, (const T *)tb.leaf, (const T *)tb.mid,
+                                   tb.stride, nleaf, nmid, sink);
                 prof_mark(ctx);
             };
-            auto by_pat = [&](auto smc) {
-                constexpr bool S = decltype(smc)::value;
-                switch (pattern) {
-                    case 0: return go(k_gather_probe<T, CPL, G, S, 0>);
-                    case 1: return go(k_gather_probe<T, CPL, G, S, 1>);
-                    case 2: return go(k_gather_probe<T, CPL, G, S, 2>);
-                    case 3: return go(k_gather_probe<T, CPL, G, S, 3>);
-                    case 4: return go(k_gather_probe<T, CPL, G, S, 4>);
-                    case 5: return go(k_gather_probe<T, CPL, G, S, 5>);
-                    case 6: return go(k_gather_probe<T, CPL, G, S, 6>);
-                    case 7: return go(k_gather_probe<T, CPL, G, S, 7>);
-                    case 8: return go(k_gather_probe<T, CPL, G, S, 8>);
-                    default: return go(k_gather_probe<T, CPL, G, S, 9>);
-                }
-            };
-            if (sm) by_pat(std::true_type{});
-            else by_pat(std::false_type{});
+            switch (pattern) {
+                case 0: return go(k_gather_probe<T, CPL, G, 0>);
+                case 1: return go(k_gather_probe<T, CPL, G, 1>);
+                case 2: return go(k_gather_probe<T, CPL, G, 2>);
+                case 3: return go(k_gather_probe<T, CPL, G, 3>);
+                case 4: return go(k_gather_probe<T, CPL, G, 4>);
+                case 5: return go(k_gather_probe<T, CPL, G, 5>);
+                case 6: return go(k_gather_probe<T, CPL, G, 6>);
+                case 7: return go(k_gather_probe<T, CPL, G, 7>);
+                case 8: return go(k_gather_probe<T, CPL, G, 8>);
+                default: return go(k_gather_probe<T, CPL, G, 9>);
+            }
+        } else {
+            throw Error{DFACTO_E_UNSUPPORTED, "no gather probe for this form"};
         }
     });
     DF_LAUNCHED();
