@@ -1103,19 +1103,14 @@ size_t tile_lds_bytes(int R) {
     return sizeof(double) * (size_t)R * R + 2 * sizeof(float) * (size_t)tile_rows(R) * (R + 1);
 }
 
-// Generic versions for any R (up to 256): rows staged in LDS, the matrix in
-// LDS when it fits.
-constexpr int kLdsMatMaxR = 64;
-
+// Generic versions for ranks above kRowAnyMaxR: rows staged in LDS, the matrix
+// read from memory (its FMAs' bound; the matrix-core kernels below would hold
+// 256 registers of it a wave at R = 256).
 template <typename Tout>
 __global__ __launch_bounds__(kBlock) void k_rowmap_g(const float *__restrict__ M, int64_t rows,
                                                      int R, const double *__restrict__ W,
                                                      Tout *__restrict__ F) {
-    __shared__ double sW[kLdsMatMaxR * kLdsMatMaxR];
     __shared__ float sM[kBlock * 4];
-    const bool wlds = R <= kLdsMatMaxR;
-    if (wlds)
-        for (int e = threadIdx.x; e < R * R; e += kBlock) sW[e] = W[e];
     const int rpp = (kBlock * 4) / R > 0 ? (kBlock * 4) / R : 1;  // rows per pass staged
     const int64_t npass = (rows + rpp - 1) / rpp;
     for (int64_t pass = blockIdx.x; pass < npass; pass += gridDim.x) {
@@ -1128,11 +1123,7 @@ __global__ __launch_bounds__(kBlock) void k_rowmap_g(const float *__restrict__ M
             const int rr = e / R, s = e % R;
             double acc = 0.0;
             const float *m = sM + rr * R;
-            if (wlds) {
-                for (int k = 0; k < R; ++k) acc = fma((double)m[k], sW[k * R + s], acc);
-            } else {
-                for (int k = 0; k < R; ++k) acc = fma((double)m[k], W[k * R + s], acc);
-            }
+            for (int k = 0; k < R; ++k) acc = fma((double)m[k], W[k * R + s], acc);
             st_out<Tout>(F, r0 * R + e, acc);
         }
     }
@@ -1143,12 +1134,8 @@ __global__ __launch_bounds__(kBlock) void k_gd_rows_g(float *__restrict__ G, con
                                                       int64_t rows, int R,
                                                       const double *__restrict__ H,
                                                       double *__restrict__ partial) {
-    __shared__ double sH[kLdsMatMaxR * kLdsMatMaxR];
     __shared__ double sF[kBlock * 2];
     __shared__ double sh[kBlock];
-    const bool hlds = R <= kLdsMatMaxR;
-    if (hlds)
-        for (int e = threadIdx.x; e < R * R; e += kBlock) sH[e] = H[e];
     const int rpp = (kBlock * 2) / R > 0 ? (kBlock * 2) / R : 1;
     const int64_t npass = (rows + rpp - 1) / rpp;
     double inner = 0.0;
@@ -1162,11 +1149,7 @@ __global__ __launch_bounds__(kBlock) void k_gd_rows_g(float *__restrict__ G, con
             const int rr = e / R, s = e % R;
             const double *f = sF + rr * R;
             double acc = 0.0;
-            if (hlds) {
-                for (int k = 0; k < R; ++k) acc = fma(f[k], sH[k * R + s], acc);
-            } else {
-                for (int k = 0; k < R; ++k) acc = fma(f[k], H[k * R + s], acc);
-            }
+            for (int k = 0; k < R; ++k) acc = fma(f[k], H[k * R + s], acc);
             const double m = (double)G[r0 * R + e];
             inner = fma(f[s], m, inner);
             G[r0 * R + e] = (float)(acc - m);
