@@ -98,7 +98,9 @@ typedef struct dfacto_allocator {
 /* Create a context on HIP device `device` that enqueues on `hip_stream`
  * (a hipStream_t; NULL = the default stream).
  * alloc: NULL, and the library allocates itself (hipMalloc for tensors and
- * workspaces, stream-ordered hipMallocAsync for build temporaries); or the
+ * workspaces, a stream-ordered memory pool of the context's for build
+ * temporaries: between builds, and until dfacto_ctx_destroy, the pool keeps up
+ * to 128 MiB of device memory for the next one); or the
  * caller's allocator, which then serves every device allocation made on the
  * context's behalf: the flattenings of the tensors it builds (which keep
  * the allocator and the context's stream of that time for their
@@ -180,7 +182,7 @@ dfacto_status dfacto_build_flattenings(dfacto_ctx *ctx, const int64_t dims[3], i
 #define DFACTO_BUILD_NO_RELABEL 2
 
 /* Default stream entries per MTTKRP work chunk (a chunk is the unit of work
- * of one lane group; it ends at the first header at or after a multiple of
+ * of one lane group, or of one block where there are few; it ends at the first header at or after a multiple of
  * the chunk length). */
 #define DFACTO_CHUNK_DEFAULT 512
 
@@ -512,8 +514,10 @@ dfacto_status dfacto_joint_grad(dfacto_ctx *ctx, const dfacto_tensor *X, const d
  *   a_i = (sum_j y_ij b_j + mu M_0[i]) (sum_j b_j^T b_j + mu B^T B * C^T C + lam I)^-1
  * over the items j rated by user i, likewise b_j over the users who rated j,
  * and c_k = mu M_2[k] (mu A^T A * B^T B + lam I)^-1.  Each user's and item's
- * R x R system is formed and inverted in FP64 by one wavefront; factors are
- * updated in place in their dtype (no column normalization).  Needs lam > 0
+ * R x R system is formed and solved in FP64, four rows to a wavefront (rows of
+ * more than 256 stream entries in segments, whose partial systems take up to
+ * 46 MB of a context workspace); factors are updated in place in their dtype
+ * (no column normalization).  Needs lam > 0
  * (every system is then positive definite) and R <= 32
  * (DFACTO_E_UNSUPPORTED above); DFACTO_E_NUMERIC if a system still fails
  * the positive-definiteness test.  Synchronizes the stream (the test's

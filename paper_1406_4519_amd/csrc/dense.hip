@@ -1,8 +1,8 @@
 // dense.hip -- the small dense FP64 parts of CP-ALS and GD (Appendix B and C)
 //
-//  * Gram F^T F of a factor or of an MTTKRP result, FP64 accumulation: on
-//    the matrix cores (FP64 MFMA) for R <= 64, else register-tiled 8x8 outer
-//    products per thread; then a fixed-order reduction over blocks.
+//  * Gram F^T F of a factor or of an MTTKRP result, FP64 accumulation on the
+//    matrix cores (FP64 MFMA), a wave's tiles in registers for R <= 64, rows
+//    staged in LDS above; then a fixed-order reduction over blocks.
 //  * H = G_p * G_q + reg I (Appendix A: (A kr B)^T (A kr B) = A^T A * B^T B,
 //    ridge term of the regularized update).
 //  * One-workgroup FP64 solve: Cholesky inverse of H, or the Moore-Penrose
@@ -13,8 +13,11 @@
 //    lambda_r^2 = [H^-1 M^T M H^-1]_rr and  <X, Xhat> = <Fhat, M> =
 //    trace(H^-1 M^T M) for the last mode; ||Xhat||^2 = lambda^T (G_A * G_B *
 //    G_C) lambda.
-//  * Row maps F = M W (W = H^-1 diag(1/lambda)) and the GD gradient
-//    -M + F H over LDS-staged row tiles, the R x R matrix broadcast from LDS.
+//  * Row maps F = M W (W = H^-1 diag(1/lambda)) and the GD gradient -M + F H:
+//    on the matrix cores up to R = 128, or over LDS-staged row tiles with the
+//    R x R matrix broadcast from LDS (some small ranks) or read from memory.
+//  * The row systems of the joint model's ALS, four to a wave on the matrix
+//    cores.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -227,9 +230,12 @@ __global__ __launch_bounds__(BS) void k_gram_mfma_group(const GramJob *__restric
 // Ranks above 64 (up to 16 column tiles, 136 tile pairs): a block takes
 // kWidePairs of the pairs (blockIdx.y), nine per wave, whose sums fill a
 // wave's registers; its rows go through LDS 16 at a time, read by all four
-// waves; bound by FP64 MFMA.  R = 100, Grams of 120,000, 61,000 and 23,000
-// rows on average: BF16 393 -> 138 us (beside the MTTKRP), FP32 330 -> 82 us,
-// against 8 x 8 register tiles on the vector units.
+// waves.  What bounds it is the wait in front of each step: with one wave a SIMD
+// and nothing prefetched a step's loads and its products take turns (R = 100,
+// 120,000 rows: 140 to 155 us, of which the products are 23 at 68 cycles each).
+// R = 100, Grams of 120,000, 61,000 and 23,000 rows on average, against 8 x 8
+// register tiles on the vector units: BF16 393 -> 133 us (beside the MTTKRP; 74
+// alone), FP32 330 -> 83 us (73 alone).
 constexpr int kWideWavePairs = 9, kWidePairs = 4 * kWideWavePairs;
 
 template <typename T, int NTMAX>
@@ -465,9 +471,11 @@ __device__ bool gauss_jordan_wave(const double *H, int R, double tol, double *Bw
 // unit column is never read again, so the column of the inverse takes its
 // place.  Operation for operation the arithmetic of the other two versions.
 // A step publishes its row, its column and 1 / pivot in LDS (two sets, so one
-// barrier per step), then every entry takes one FMA: R steps of about 0.3 us,
-// where sweeping [H | I] in global memory took 28 us each (R = 100: 2782 -> 101
-// us beside the MTTKRP).
+// barrier per step), then every entry takes one FMA: R steps of 0.6 us, where
+// sweeping [H | I] in global memory took 28 us each (R = 100: 2782 -> 98 us
+// beside the MTTKRP).  Alone the solve takes 84 us there, 60 of them the steps;
+// the rest forms H in global scratch and symmetrizes the inverse from it
+// (R = 128: 114 and 77; R = 64: 43).
 template <int NT>
 __device__ bool gauss_jordan_block(const double *__restrict__ Gp, const double *__restrict__ Gq,
                                    double reg, int R, double tol, double *__restrict__ Bw) {
@@ -789,7 +797,7 @@ __device__ void als_lambda_body(int R, int mode, const double *__restrict__ Hinv
 // The lambda step of ranks above kLambdaSmemMaxR, spread over the device: one
 // block formed both R x R x R products from global memory (R = 100: 1103 us);
 // here each of the two takes a block per 16 x 16 tile, its operands staged in
-// LDS, and the rest one block (two products of 9 us and 27 us).  Every entry's sum runs over k in order, so the
+// LDS, and the rest one block (two products of 9 us and 27 us at R = 100).  Every entry's sum runs over k in order, so the
 // results are bitwise those of als_lambda_body.
 constexpr int kMulTile = 16, kMulK = 64;
 // C = A B (R x R, row-major)
@@ -1276,7 +1284,8 @@ __device__ __forceinline__ void store4d(uint16_t *p, const double4v &a) {
 //
 // What bounds it: FP64 issue -- 44 products of 16 cycles per four entries of
 // four rows, and 250 products with about as much scalar-pivot arithmetic per
-// solve of four -- at three waves a SIMD (168 registers).  One row a wave with
+// solve of four -- at three waves a SIMD (168 registers; at R > 16 k_joint_rows
+// keeps 17 to 19 more, and 32 to 34 scalars, in scratch).  One row a wave with
 // the columns broadcast through LDS was bound by LDS bandwidth, one 512-byte
 // broadcast read per multiply-add.  10M + 4M nonzeros, 400K users, 200K items,
 // R = 32, users and items together: rows 4594 -> 1206 us, split rows (segments

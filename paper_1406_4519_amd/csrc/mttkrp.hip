@@ -51,7 +51,7 @@ namespace {
     __attribute__((amdgpu_waves_per_eu(G <= 32 ? (CPL >= 8 ? 4 : DFACTO_WAVES_PER_EU) : 1)))
 
 constexpr int kBlock = 256;
-constexpr int kUnroll = DFACTO_UNROLL;  // stream entries in flight per group
+constexpr int kUnroll = DFACTO_UNROLL;  // the residual kernel's entries in flight per group
 static_assert(kStreamPad >= kUnroll && kStreamPad >= 32, "stream padding must cover a batch");
 
 // f(integral_constant<int, I>) for I = B .. E-1, so I is usable as a constant
@@ -514,11 +514,17 @@ __device__ __forceinline__ void mttkrp_res_chunk(const uint2 *__restrict__ st_,
 // group's lanes; a masked FMA then costs one vector instruction per column
 // and nothing where it does not apply (about 20 per entry in all).  The lane
 // that loads an entry also forms its row's address, once for its group.
-// What bounds it at scale: lines past L2, 128 bytes for every gathered row
-// that misses (R = 8 to 32 take the same time), at about 6 TB/s.  Three modes
-// of the 50M-nonzero Zipf(1.1) tensor: R = 32 FP32 2140 -> 2060 us, BF16
-// 2046 -> 1905, R = 8 2181 -> 1799; 100M nonzeros relabeled, R = 32 BF16
-// 3244 -> 2948, R = 10 FP32 3108 -> 3043, R = 100 BF16 11018 -> 8250.
+// What bounds it at scale: the misses of its gathers.  Its loads alone (the
+// gather probe's pattern 0) take 91 to 100% of its time, and two rates limit
+// them: lines from beyond L2 (uniformly drawn rows of the same tables get 53 to
+// 56 G/s, 6.8 to 7.2 TB/s of 128-byte lines) and L1 misses (rows that all lie
+// in L2: 142 to 150 G/s).  By the counters, R = 32: 50M nonzeros 47.8 G/s (FP32)
+// and 50.5 (BF16) from beyond L2, 91 and 93% of that limit, and 104 and 105 G/s
+// L1 misses, 70 and 74%; 100M relabeled 43.3 and 40.8 (80 and 72%), 111 and 108
+// (74 and 75%).  R = 8 to 32 take nearly the same time: a row is one line.
+// Three modes, before and after: 50M, R = 32 FP32 2140 -> 2060 us, BF16 2046 ->
+// 1905, R = 8 2181 -> 1799; 100M relabeled, R = 32 BF16 3244 -> 2948, R = 10
+// FP32 3108 -> 3043, R = 100 BF16 11018 -> 8250.
 //
 // p += v * g in the lanes of `m` (V: the constraint of v, "v" or "s")
 #define DF_MASKED_ADD(V)                                                                       \
@@ -1455,12 +1461,13 @@ struct Tables {
 };
 
 // The block-per-chunk kernel where it is the faster one (false: not launched).
-// Its time grows by about 10 ns per block (8 columns; 14 ns for 16) from 11 us,
-// while the lane groups take 60-75 us however few chunks there are, until
-// about 6000 chunks fill the device.  Three modes of 20,000 nonzeros, R = 8:
-// 33 us against 141 (200 before either); 1M nonzeros (3902 chunks per mode),
-// R = 8 119 against 195, R = 16 170 against 193, but R = 32 (two slices) 290
-// against 185; 3M (8500 chunks), R = 8 314 against 216.
+// A mode takes about 10 us and 8 ns per block (8 columns; 11 ns for 16), the
+// lane groups 50 to 65 us however few chunks there are, until about 6000 chunks
+// fill the device.  Three modes, FP32, by blocks and by lane groups: 78 chunks,
+// R = 8 41 and 156 us (a pass limited by its launches); 1950, R = 8 82 and 187,
+// R = 16 97 and 187, R = 32 (two slices) 159 and 174; 3902, R = 8 125 and 193,
+// R = 16 161 and 191, but R = 32 283 and 180; 5464, R = 8 158 and 197, R = 16
+// 206 and 192; 7806, R = 8 209 and 206, R = 16 281 and 204.
 bool launch_block(dfacto_ctx *ctx, const ModeData &md, int R, dfacto_dtype dtype,
                   const MttkrpShape &sh, const Tables &tb, float *out, float *carry) {
     if (md.chunk_len > DFACTO_CHUNK_DEFAULT) return false;

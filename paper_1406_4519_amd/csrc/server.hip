@@ -269,9 +269,10 @@ size_t footprint_estimate(const dfacto_request &r) {
     return b;
 }
 
-// Peak transient device memory of building the flattenings: COO staging,
-// sort keys and permutations, gathered copies (about 80 bytes per nonzero
-// with buffers reused within the build), plus the build's arena of small
+// Peak transient device memory of building the flattenings: COO staging and
+// the sorted (key, value) pairs of every mode, or keys, permutations and
+// gathered copies where a key has more than 64 bits (at most about 80 bytes per
+// nonzero with buffers reused within the build), plus the build's arena of small
 // temporaries, which are kept until the build ends (at most about 160 bytes
 // per nonzero and 24 per row, doubled for chunk rounding, and at most a
 // few chunks of up to 1 GB).
